@@ -105,6 +105,23 @@ struct Comp {
   __device__ __forceinline__ double value() const { return s + c; }
 };
 
+// copy n 16-byte chunks global -> LDS (whole workgroup)
+__device__ __forceinline__ void copy16(void* dst, const void* src, int bytes) {
+  const int4* s = (const int4*)src;
+  int4* d = (int4*)dst;
+  const int n = bytes / 16;
+  int k = threadIdx.x;
+  // 8 loads in flight per thread before their stores
+  for (; k + 7 * (int)blockDim.x < n; k += 8 * blockDim.x) {
+    int4 t[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) t[q] = s[k + q * blockDim.x];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) d[k + q * blockDim.x] = t[q];
+  }
+  for (; k < n; k += blockDim.x) d[k] = s[k];
+}
+
 // Wave (64-lane) sum of a double using cross-lane shuffles; lane 0 holds it.
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll

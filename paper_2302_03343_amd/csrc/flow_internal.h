@@ -419,23 +419,6 @@ __device__ __forceinline__ float cdf_inv(const f32x16& q, float v, float sum, in
   return ((float)bb + frac) * (1.0f / (float)FK);
 }
 
-// copy n 16-byte chunks global -> LDS (whole workgroup)
-__device__ __forceinline__ void copy16(void* dst, const void* src, int bytes) {
-  const int4* s = (const int4*)src;
-  int4* d = (int4*)dst;
-  const int n = bytes / 16;
-  int k = threadIdx.x;
-  // 8 loads in flight per thread before their stores
-  for (; k + 7 * (int)blockDim.x < n; k += 8 * blockDim.x) {
-    int4 t[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) t[q] = s[k + q * blockDim.x];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) d[k + q * blockDim.x] = t[q];
-  }
-  for (; k < n; k += blockDim.x) d[k] = s[k];
-}
-
 // ---------------------------------------------------------------------------
 // Forward kernels: MODE 0 density (eval), 1 density (training), 2 sampling.
 // ---------------------------------------------------------------------------

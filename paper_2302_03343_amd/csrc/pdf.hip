@@ -14,6 +14,7 @@
 // knots) is one contiguous 4*n_flav run.  Knots are staged in LDS for the
 // binary searches; outputs are written structure-of-arrays, coalesced.
 #include "pdf_internal.h"
+#include "pdf_lds.h"
 
 #include <float.h>
 #include <math.h>
@@ -552,6 +553,57 @@ __global__ __launch_bounds__(256) void k_alphas(AlphasArgs g, int64_t n, const d
 
 using namespace vgx;
 
+namespace {
+
+// The kernels with the grid in LDS may take all of a CU's LDS.
+template <int M>
+hipError_t allow_lds() {
+  for (const void* k : {reinterpret_cast<const void*>(&k_pdf_interp_lds<double, double, M, false>),
+                        reinterpret_cast<const void*>(&k_pdf_interp_lds<double, double, M, true>),
+                        reinterpret_cast<const void*>(&k_pdf_interp_lds<float, float, M, false>)}) {
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsCap);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+// The tables of the interpolation with the grid in LDS (sync): uploaded, and
+// member 0's nodes regrouped on the device.
+vgx_status setup_lds(vgx_pdf* p, const double* lx, const double* lq, hipStream_t st) {
+  PdfLdsArgs a{};
+  if (!pdf_lds_plan(p, a)) return VGX_OK;
+  const int n_nodes = p->n_x * p->q_off[p->n_sub];
+  const int g64 = (p->n_flav + 1) / 2, g32 = (p->n_flav + 3) / 4;
+  const size_t ratios = 16 * (size_t)(a.x.n + a.q.n);
+  p->lds_o_ratios = (size_t)a.tab_bytes;
+  p->lds_o_n64 = p->lds_o_ratios + ratios;
+  p->lds_o_n32 = p->lds_o_n64 + (size_t)g64 * a.node_bytes;
+  unsigned char* h = (unsigned char*)malloc(p->lds_o_n64);
+  if (!h) { set_error("pdf_create: host allocation failed"); return VGX_ENOMEM; }
+  pdf_lds_fill(p, a, lx, lq, h, (double*)(h + p->lds_o_ratios));
+  vgx_status s = dev_alloc((void**)&p->lds_block, p->lds_o_n32 + (size_t)g32 * a.node_bytes);
+  if (s == VGX_OK) {
+    hipError_t e = hipMemcpyAsync(p->lds_block, h, p->lds_o_n64, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) {
+      hipLaunchKernelGGL(k_pdf_group<double>, dim3((g64 * n_nodes * 2 + 255) / 256), dim3(256), 0, st, p->v64, n_nodes,
+                         p->n_flav, g64, (double*)(p->lds_block + p->lds_o_n64));
+      hipLaunchKernelGGL(k_pdf_group<float>, dim3((g32 * n_nodes * 4 + 255) / 256), dim3(256), 0, st, p->v32, n_nodes,
+                         p->n_flav, g32, (float*)(p->lds_block + p->lds_o_n32));
+      e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = allow_lds<VGX_EXTRAP_ERROR>();
+    if (e == hipSuccess) e = allow_lds<VGX_EXTRAP_FREEZE>();
+    if (e == hipSuccess) e = allow_lds<VGX_EXTRAP_CONTINUE>();
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) s = hip_fail(e, "pdf_create tables", __FILE__, __LINE__);
+  }
+  free(h);
+  p->lds_args = a;
+  return s;
+}
+
+}  // namespace
+
 extern "C" vgx_status pdf_create(const vgx_pdf_desc* d, void* stream, vgx_pdf** out) {
   return pdf_create_set(d, 1, stream, out);
 }
@@ -660,11 +712,57 @@ extern "C" vgx_status pdf_create_set(const vgx_pdf_desc* d, int32_t n_members, v
     if (e == hipSuccess) e = hipMemsetAsync(p->oor, 0, sizeof(unsigned long long), st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) st_ = hip_fail(e, "pdf_create copies", __FILE__, __LINE__);
+    if (st_ == VGX_OK) st_ = setup_lds(p, lx, lq, st);
   } while (0);
   free(lx); free(lq); free(v); free(v32);
   if (st_ != VGX_OK) { pdf_destroy(p); return st_; }
   *out = p;
   return VGX_OK;
+}
+
+// Queries from which the kernel with the grid in LDS is taken, and from which
+// its FP64 variant takes all groups in turn (evenly spaced synthetic grid of
+// 196 x 50 nodes, 11 flavours, us per call, gathers / one group per workgroup
+// / all groups): at 2e4 both are bound by the launch (9.6 / 9.0 in FP32), at
+// 1e5 FP64 15.0 / 11.7, FP32 12.4 / 10.5; at 1e6 FP64 80 / 65 / 65, FP32 63 /
+// 42; at 3e7 FP64 2542 / 1865 / 1560, FP32 1770 / 1047.
+constexpr int64_t kLdsMinQueries = 16384;
+constexpr int64_t kLdsAllGroups = 1000000;
+// Queries a workgroup locates at a time: the staging of six groups per tile
+// (6 x 157 KB) against the records' reach of the caches; 8192 to 131072
+// measured within 3 %.
+constexpr int64_t kLdsTile = 32768;
+
+template <int M>
+static void launch_interp_lds(const vgx_pdf* p, hipStream_t st, int64_t n, const double* x_dev, const double* q2_dev,
+                              int32_t out_dtype, void* out_dev) {
+  PdfLdsArgs a = p->lds_args;
+  const int v = out_dtype == VGX_F64 ? 2 : 4;
+  const int cus = device_cus();
+  a.groups = (p->n_flav + v - 1) / v;
+  const bool all = out_dtype == VGX_F64 && n >= kLdsAllGroups && p->n_flav >= 2;
+  if (all) {
+    a.wg_full = cus;
+    const int64_t share = (n + cus - 1) / cus, rounds = (share + kLdsTile - 1) / kLdsTile;
+    a.tile = (int)(((share + rounds - 1) / rounds + kLdsBlock - 1) / kLdsBlock * kLdsBlock);
+  } else {
+    // a last group with flavours missing costs less: locating a query and the
+    // stencil weights are the same, the reads and sums are fewer
+    const int rem = p->n_flav % v;
+    const double last = rem ? 0.7 + 0.3 * rem / v : 1.0;
+    a.wg_full = a.groups > 1 ? (int)(cus / (a.groups - 1 + last) + 0.5) : cus;
+  }
+  const size_t lds = (size_t)a.node_bytes + a.tab_bytes;
+  const unsigned char* b = p->lds_block;
+  const double2* ratios = (const double2*)(b + p->lds_o_ratios);
+  if (out_dtype == VGX_F64) {
+    auto k = all ? k_pdf_interp_lds<double, double, M, true> : k_pdf_interp_lds<double, double, M, false>;
+    hipLaunchKernelGGL(k, dim3(cus), dim3(kLdsBlock), lds, st, a, n, x_dev, q2_dev, b, b + p->lds_o_n64, ratios,
+                       (double*)out_dev, p->oor);
+  } else {
+    hipLaunchKernelGGL((k_pdf_interp_lds<float, float, M, false>), dim3(cus), dim3(kLdsBlock), lds, st, a, n, x_dev,
+                       q2_dev, b, b + p->lds_o_n32, ratios, (float*)out_dev, p->oor);
+  }
 }
 
 template <int M>
@@ -703,9 +801,16 @@ extern "C" vgx_status pdf_interp(const vgx_pdf* p, int64_t n, const double* x_de
   const int grid = (int)(want < (int64_t)device_cus() * 8 ? want : (int64_t)device_cus() * 8);
   const size_t lds = pdf_interp_lds_bytes(p->n_x, p->q_off[p->n_sub], p->n_flav);
   hipStream_t st = (hipStream_t)stream;
+  // outputs over the queries: only the gather kernel reads a query before any of its outputs is written
+  const char *o = (const char*)out_dev, *oe = o + (size_t)n * p->n_flav * (out_dtype == VGX_F64 ? 8 : 4);
+  const bool in_place = ((const char*)x_dev < oe && o < (const char*)(x_dev + n)) ||
+                        ((const char*)q2_dev < oe && o < (const char*)(q2_dev + n));
   auto launch = [&](auto mode_tag) {
     constexpr int M = decltype(mode_tag)::value;
-    launch_interp<M>(p, g, dim3(grid), block, lds, st, n, x_dev, q2_dev, out_dtype, out_dev);
+    if (p->lds_block && n >= kLdsMinQueries && !in_place)
+      launch_interp_lds<M>(p, st, n, x_dev, q2_dev, out_dtype, out_dev);
+    else
+      launch_interp<M>(p, g, dim3(grid), block, lds, st, n, x_dev, q2_dev, out_dtype, out_dev);
   };
   if (p->extrap == VGX_EXTRAP_FREEZE) launch(std::integral_constant<int, VGX_EXTRAP_FREEZE>{});
   else if (p->extrap == VGX_EXTRAP_CONTINUE) launch(std::integral_constant<int, VGX_EXTRAP_CONTINUE>{});
@@ -809,7 +914,7 @@ extern "C" vgx_status pdf_bounds(const vgx_pdf* p, double* xmin, double* xmax, d
 extern "C" void pdf_destroy(vgx_pdf* p) {
   if (!p) return;
   hipFree(p->x); hipFree(p->lx); hipFree(p->q2); hipFree(p->lq2);
-  hipFree(p->v64); hipFree(p->v32); hipFree(p->oor);
+  hipFree(p->v64); hipFree(p->v32); hipFree(p->oor); hipFree(p->lds_block);
   hipFree(p->a_lq2); hipFree(p->a_val);
   free(p->h_x); free(p->h_q2); free(p->h_aq2); free(p->h_aval);
   delete p;

@@ -7,6 +7,29 @@
 #define VGX_MAX_SUB 8
 #define VGX_MAX_FLAV 16
 
+namespace vgx {
+
+// One axis of a query located in LDS (pdf_lds.h): the start-cell bucket of a
+// value whose FP64 top word is w is (w - w0) >> shift.
+struct PdfLdsAxis {
+  int n;  // knots (subgrids concatenated)
+  int w0, shift;
+  double lo, hi;
+};
+
+// The interpolation kernel with the grid in LDS: byte offsets of its tables
+// (after the nodes), and the split of the workgroups over flavour groups.
+struct PdfLdsArgs {
+  PdfLdsAxis x, q;
+  int n_flav, groups;
+  int wg_full;                  // one group per workgroup: workgroups per full group (the last takes the rest)
+  int tile;                     // all groups in turn: queries a workgroup locates at a time
+  int node_bytes, tab_bytes;    // one group's nodes; the tables
+  int o_kx, o_kq, o_hx, o_hq, o_log, o_bx, o_bq;
+};
+
+}  // namespace vgx
+
 struct vgx_pdf {
   int device = 0;
   int n_x = 0, n_sub = 0, n_flav = 0;
@@ -27,6 +50,11 @@ struct vgx_pdf {
                                       // is what pdf_interp and the fused integrands read
   float* v32 = nullptr;               // same, FP32 copy
   unsigned long long* oor = nullptr;  // out-of-range counter
+  // tables of the interpolation with the grid in LDS (member 0), in one
+  // block; null where a grid does not fit
+  unsigned char* lds_block = nullptr;
+  vgx::PdfLdsArgs lds_args{};
+  size_t lds_o_ratios = 0, lds_o_n64 = 0, lds_o_n32 = 0;
   // alpha_s(Q) table (optional; pdf_set_alphas): knots on the Q^2 line split
   // into subgrids at duplicated knots
   int a_nsub = 0;
