@@ -11,13 +11,17 @@
 // every store of a wave is contiguous.  Uniforms: Philox-4x32-10 with the
 // counter of sample e of the VEGAS kernels (low and high words of e, the
 // iteration, stream << 8 | block), block i giving particle i's four numbers.
-// Massive momenta: xi by Newton's method from xi0 = sqrt(1 - (sum m/sqrt s)^2),
-// where the (convex, increasing) constraint is >= 0, so the iterates approach
-// the root from above.  The constraint is evaluated in FP64; its derivative
-// only sets the step length and takes the hardware reciprocal (relative error
-// about 2^-23), which keeps the convergence quadratic down to 2^-23 of the
-// step.  The loop ends after a step below 2^-30 of xi: the error left is then
-// of the order of xi's own rounding.
+// Massive momenta: xi from xi0 = sqrt(1 - (sum m/sqrt s)^2) by Chebyshev's
+// third-order method (Newton's step u, then u (1 + u f''/(2 f'))), which takes
+// two iterations where Newton's takes four; it ends after a step below 2^-20
+// of xi, whose cube is far below xi's rounding.  Massless particles add xi E to
+// the constraint and take no square root.
+//
+// Both kernels were bound by the FP64 VALU work of the library's log, sincospi,
+// sqrt and divisions (1020 and 1608 instructions per event at n = 4); math64.h
+// has forms for the ranges that occur here (about 800 and 900).  1e7 events
+// of 4: massless 0.34 -> 0.25 ms (5.4 TB/s of the 136 bytes an event that are
+// written: the HBM's rate for 17 streams), massive 0.51 -> 0.34 ms (VALU).
 //
 // Unweighting: w_max by a max over the positive weights (block maxima, then
 // one workgroup over those: exact in any order);
@@ -25,6 +29,7 @@
 // counts (keeping each wave's ballot of its decisions), one exclusive scan,
 // and a scatter that ranks the kept events from the ballots.
 #include "common.h"
+#include "math64.h"
 
 #include <math.h>
 #include <string.h>
@@ -38,6 +43,7 @@ constexpr int RB_BLOCK = 256;
 struct RamboArgs {
   int64_t n_events, first;
   double sqrt_s, w0, w0m, sum_m;  // w0m = w0 s^(2-n), the massive weight's constant
+  double xi0;                     // sqrt(1 - (sum m/sqrt s)^2)
   double m[VGX_MAX_PART];
   uint32_t k0, k1, sid, it;
 };
@@ -58,6 +64,9 @@ __device__ __forceinline__ double ipow(double x) {
 
 template <int N, bool MASSIVE>
 __global__ __launch_bounds__(RB_BLOCK) void k_rambo(RamboArgs a, double* __restrict__ mom, double* __restrict__ wout) {
+  __shared__ M64Tables tab;
+  m64_tables(tab);
+  __syncthreads();
   const int64_t stride = (int64_t)gridDim.x * RB_BLOCK;
   for (int64_t e = (int64_t)blockIdx.x * RB_BLOCK + threadIdx.x; e < a.n_events; e += stride) {
     const uint64_t idx = (uint64_t)(a.first + e);
@@ -67,10 +76,10 @@ __global__ __launch_bounds__(RB_BLOCK) void k_rambo(RamboArgs a, double* __restr
     for (int i = 0; i < N; ++i) {
       const u32x4 r = philox4x32_10((uint32_t)idx, (uint32_t)(idx >> 32), a.it, (a.sid << 8) | (uint32_t)i, a.k0, a.k1);
       const double c = 2.0 * word_to_unit(r.x) - 1.0;
-      const double e0 = -log(word_to_unit(r.z) * word_to_unit(r.w));
-      const double st = sqrt(1.0 - c * c);
+      const double e0 = -m64_log(tab, word_to_unit(r.z) * word_to_unit(r.w));
+      const double st = m64_root(1.0 - c * c).g;  // c is never +-1
       double sn, cs;
-      sincospi(2.0 * word_to_unit(r.y), &sn, &cs);  // phi = 2 pi u, without a reduction modulo 2 pi
+      m64_sincos(tab, r.y, sn, cs);
       q[i][0] = e0;
       q[i][1] = e0 * st * cs;
       q[i][2] = e0 * st * sn;
@@ -81,10 +90,9 @@ __global__ __launch_bounds__(RB_BLOCK) void k_rambo(RamboArgs a, double* __restr
       Q3 += q[i][3];
     }
     // boost and scale onto P = (sqrt s, 0): p = x H_b(q)
-    const double M = sqrt(Q0 * Q0 - Q1 * Q1 - Q2 * Q2 - Q3 * Q3);
-    const double iM = 1.0 / M;
+    const double iM = m64_rsqrt(Q0 * Q0 - Q1 * Q1 - Q2 * Q2 - Q3 * Q3);
     const double b1 = -Q1 * iM, b2 = -Q2 * iM, b3 = -Q3 * iM;
-    const double x = a.sqrt_s * iM, gam = Q0 * iM, aa = 1.0 / (1.0 + gam);
+    const double x = a.sqrt_s * iM, gam = Q0 * iM, aa = m64_rcp(1.0 + gam);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const double bq = b1 * q[i][1] + b2 * q[i][2] + b3 * q[i][3];
@@ -96,32 +104,46 @@ __global__ __launch_bounds__(RB_BLOCK) void k_rambo(RamboArgs a, double* __restr
     }
     double w = a.w0;
     if constexpr (MASSIVE) {
-      // sum_i sqrt(m_i^2 + xi^2 E_i^2) = sqrt s
-      const double t = a.sum_m / a.sqrt_s;
-      double xi = sqrt(1.0 - t * t);
+      // sum_i sqrt(m_i^2 + xi^2 E_i^2) = sqrt s; a massless particle's term is xi E_i
+      double xi = a.xi0;
       for (int iter = 0; iter < 64; ++iter) {
-        double f = -a.sqrt_s, fp = 0.0;
+        double f = -a.sqrt_s, fp = 0.0, fpp = 0.0;
 #pragma unroll
         for (int i = 0; i < N; ++i) {
-          const double xe = xi * q[i][0];
-          const double k0 = sqrt(a.m[i] * a.m[i] + xe * xe);
-          f += k0;
-          fp += xe * q[i][0] * __builtin_amdgcn_rcp(k0);
+          const double E = q[i][0], xe = xi * E;
+          if (a.m[i] == 0.0) {
+            f += xe;
+            fp += E;
+          } else {
+            const double m2 = a.m[i] * a.m[i];
+            const Root64 k = m64_root(fma(xe, xe, m2));
+            const double t = E * k.y;
+            f += k.g;
+            fp = fma(xe, t, fp);
+            fpp = fma(t * t, m2 * k.y, fpp);
+          }
         }
-        const double step = f * __builtin_amdgcn_rcp(fp);
-        xi -= step;
-        if (!(fabs(step) >= 0x1p-30 * xi)) break;
+        const double ifp = m64_rcp(fp), step = f * ifp;
+        xi = fma(-step, fma(0.5 * step, fpp * ifp, 1.0), xi);
+        if (!(fabs(step) >= 0x1p-20 * xi)) break;
       }
       double sk = 0.0, pr = 1.0, sk2 = 0.0;
 #pragma unroll
       for (int i = 0; i < N; ++i) {
         const double kabs = xi * q[i][0];  // |k_i| = xi |p_i| = xi p_i^0 (p_i massless)
-        const double k0 = sqrt(a.m[i] * a.m[i] + kabs * kabs);
-        const double ik = 1.0 / k0;
         sk += kabs;
-        pr *= kabs * ik;
-        sk2 += kabs * kabs * ik;
-        q[i][0] = k0;
+        if (a.m[i] == 0.0) {
+          sk2 += kabs;
+          q[i][0] = kabs;
+        } else {
+          const double k2 = fma(kabs, kabs, a.m[i] * a.m[i]);
+          const Root64 k = m64_root(k2);
+          double v = kabs * k.y;  // |k_i|/k_i^0, corrected by the remainder
+          v = fma(fma(-v, k.g, kabs), k.y, v);
+          pr *= v;
+          sk2 = fma(kabs, v, sk2);
+          q[i][0] = k.g;
+        }
         q[i][1] *= xi;
         q[i][2] *= xi;
         q[i][3] *= xi;
@@ -368,6 +390,8 @@ extern "C" vgx_status rambo_generate(int32_t n_part, const double* masses, doubl
   // w0 = (2 pi)^(4-3n) (pi/2)^(n-1) s^(n-2) / (Gamma(n) Gamma(n-1))
   a.w0m = pow(2.0 * M_PI, 4.0 - 3.0 * n) * pow(M_PI / 2.0, n - 1.0) / (tgamma((double)n) * tgamma(n - 1.0));
   a.w0 = a.w0m * pow(s, n - 2.0);
+  const double t = a.sum_m / sqrt_s;
+  a.xi0 = sqrt(1.0 - t * t);
   a.k0 = (uint32_t)seed;
   a.k1 = (uint32_t)(seed >> 32);
   a.sid = stream_id;
