@@ -28,6 +28,16 @@ struct Combined {
 
 constexpr int MAX_RECORDS = 4096;
 
+// Where a kernel leaves a completed record for the host: pinned host memory
+// mirroring the records and the combination, and a word that takes `seq` once
+// both are visible there.  flag null: the device copies only.
+struct HostOut {
+  IterRecord* rec;
+  Combined* comb;
+  unsigned long long* flag;
+  unsigned long long seq;
+};
+
 // Grid map (inverse transform through the piecewise-constant density of the
 // bins): i = min(floor(u N), N-1), delta = u N - i,
 // x = e_i + delta (e_{i+1} - e_i), J = prod_j N (e_{i+1} - e_i).
@@ -150,8 +160,10 @@ __device__ __forceinline__ Comp wave_merge(Comp a) {
 // chi^2/dof = sum (E_i - E_bar)^2/S_i^2/(M-1).  A zero variance makes that
 // estimate exact (sigma 0).  Called by the 64 lanes of one wave, which split
 // the records (lane l takes l, l+64, ...) so that the cost per iteration does
-// not grow with the number of stored estimates; lane 0 writes the results.
-__device__ inline void finalize_record(double s1, double s2, int64_t n, IterRecord* rec, int k_rec, Combined* comb) {
+// not grow with the number of stored estimates; lane 0 writes the results,
+// with host.flag set also to the host.
+__device__ inline void finalize_record(double s1, double s2, int64_t n, IterRecord* rec, int k_rec, Combined* comb,
+                                       const HostOut& host = {}) {
   // no contraction into FMAs, so that every kernel that inlines this gives the same bits
 #pragma clang fp contract(off)
   const int lane = threadIdx.x & 63;
@@ -225,7 +237,15 @@ __device__ inline void finalize_record(double s1, double s2, int64_t n, IterReco
       c.chi2_dof = chi.value() / (double)(used - 1);
     }
   }
-  if (lane == 0) *comb = c;
+  if (lane == 0) {
+    *comb = c;
+    if (host.flag) {
+      host.rec[k_rec] = r;
+      *host.comb = c;
+      __threadfence_system();
+      __hip_atomic_store(host.flag, host.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+  }
 }
 
 // Lepage's refinement of one dimension, by one 64-thread workgroup:
@@ -296,6 +316,14 @@ __device__ inline void refine_dim(double* __restrict__ ej, const double* __restr
   }
 }
 
+// The context's pinned memory; the grid [dim][nb+1] follows.
+struct PinnedHost {
+  IterRecord rec[MAX_RECORDS];
+  Combined comb;
+  unsigned long long flag;
+  double grid[1];
+};
+
 }  // namespace vgx
 
 struct vgx_vegas {
@@ -320,13 +348,17 @@ struct vgx_vegas {
   int table_bytes = 0;
   vgx::IterRecord* rec = nullptr;   // [MAX_RECORDS]
   vgx::Combined* comb = nullptr;
-  void* pinned = nullptr;           // host readback (IterRecord + Combined + grid)
+  void* pinned = nullptr;           // host memory the device writes: PinnedHost
   int n_rec = 0;
+  bool rec_host = true;             // the host mirror holds every record
+  bool tail = false;                // the stream may still be writing the histogram of a record read, or a grid set
+  unsigned long long seq = 0;       // records read back through the mirror's flag
   bool comb_fresh = false;           // the host copy of the combination (in pinned) is current
   int pend_k = -1;                  // record holding only S1, S2 until the next refinement completes it (< 0: none)
   int64_t pend_n = 0;               // its sample count
   double judge_var = -1.0;          // n var(E) of the latest plain iteration read back (< 0: none)
   bool have_hist = false;
+  vgx::PinnedHost* host() const { return (vgx::PinnedHost*)pinned; }
   // kernel timing: event pairs recorded around the fused kernel, read back
   // (and summed) only when asked for, so timing does not synchronise
   static constexpr int kTimerPairs = 256;
