@@ -11,6 +11,8 @@
 #include "singletop.h"
 #include "ttbar_dyn.h"
 
+#include <type_traits>
+
 namespace vgx {
 
 struct IterRecord {
@@ -141,16 +143,38 @@ __device__ __forceinline__ double grid_map_t(const double (&t)[D], const double*
   return jw * nbD;
 }
 
-// Butterfly merge of compensated sums over the 64 lanes of a wave, in a fixed
-// order (partner distance 1, 2, 4, ..., 32).
-__device__ __forceinline__ Comp wave_merge(Comp a) {
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) {
-    const double os = __shfl_xor(a.s, m, 64), oc = __shfl_xor(a.c, m, 64);
+// The value of another lane by a DPP control word (a few cycles, where a
+// shuffle goes through the LDS); lanes without a source read zero.
+template <int CTRL>
+__device__ __forceinline__ double dpp_get(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;              // quad_perm [1,0,3,2], [2,3,0,1]
+constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;    // lane i <- 7 - i of 8, 15 - i of 16
+
+// Merge of compensated sums over the first `lanes` lanes of a wave (the
+// others hold zeros) into lane 0, in a fixed order: pairs, quads, eights,
+// sixteens by DPP, then across the rows of 16.  Levels beyond `lanes`
+// (uniform) would add zeros and are skipped.
+__device__ __forceinline__ Comp wave_merge(Comp a, int lanes) {
+  auto level = [&](double os, double oc) {
     a.add(os);
     a.c += oc;
-  }
+  };
+  if (lanes > 1) level(dpp_get<kDppXor1>(a.s), dpp_get<kDppXor1>(a.c));
+  if (lanes > 2) level(dpp_get<kDppXor2>(a.s), dpp_get<kDppXor2>(a.c));
+  if (lanes > 4) level(dpp_get<kDppHalfMirror>(a.s), dpp_get<kDppHalfMirror>(a.c));
+  if (lanes > 8) level(dpp_get<kDppMirror>(a.s), dpp_get<kDppMirror>(a.c));
+  if (lanes > 16) level(__shfl_xor(a.s, 16, 64), __shfl_xor(a.c, 16, 64));
+  if (lanes > 32) level(__shfl_xor(a.s, 32, 64), __shfl_xor(a.c, 32, 64));
   return a;
+}
+
+__device__ __forceinline__ double first_lane(double v) {
+  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                          __builtin_amdgcn_readfirstlane(__double2loint(v)));
 }
 
 // Estimate of one iteration from its compensated sums, stored as record
@@ -195,24 +219,20 @@ __device__ inline void finalize_record(double s1, double s2, int64_t n, IterReco
     var = rec[k].var;
     return rec[k].finite;
   };
+  const int lanes = k_rec + 1 < 64 ? k_rec + 1 : 64;
   int used = 0, zero_var = MAX_RECORDS;
   Comp wsum, msum;
-  for (int k = lane; k <= k_rec; k += 64) {
-    double mean, var;
-    if (!mean_var(k, mean, var)) continue;
-    ++used;
-    if (var == 0.0) {
-      zero_var = k < zero_var ? k : zero_var;
-    } else {
+  for (int k0 = 0; k0 <= k_rec; k0 += 64) {
+    const int k = k0 + lane;
+    double mean = 0.0, var = 1.0;
+    const bool ok = k <= k_rec && mean_var(k, mean, var);
+    const unsigned long long zeros = __ballot(ok && var == 0.0);
+    used += __popcll(__ballot(ok));
+    if (zeros && zero_var == MAX_RECORDS) zero_var = k0 + __ffsll(zeros) - 1;
+    if (ok && var != 0.0) {
       wsum.add(1.0 / var);
       msum.add(mean / var);
     }
-  }
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) {
-    used += __shfl_xor(used, m, 64);
-    const int o = __shfl_xor(zero_var, m, 64);
-    zero_var = o < zero_var ? o : zero_var;
   }
   Combined c{0.0, 0.0, 0.0, used, 0};
   if (zero_var < MAX_RECORDS) {
@@ -220,11 +240,11 @@ __device__ inline void finalize_record(double s1, double s2, int64_t n, IterReco
     mean_var(zero_var, mean, var);
     c.mean = mean;
   } else if (used > 0) {
-    wsum = wave_merge(wsum);
-    msum = wave_merge(msum);
+    wsum = wave_merge(wsum, lanes);
+    msum = wave_merge(msum, lanes);
     // lane 0's combination is the one written; every lane uses it
-    c.mean = __shfl(msum.value() / wsum.value(), 0, 64);
-    c.sigma = sqrt(1.0 / __shfl(wsum.value(), 0, 64));
+    c.mean = first_lane(msum.value() / wsum.value());
+    c.sigma = sqrt(1.0 / first_lane(wsum.value()));
     if (used > 1) {
       Comp chi;
       for (int k = lane; k <= k_rec; k += 64) {
@@ -233,7 +253,7 @@ __device__ inline void finalize_record(double s1, double s2, int64_t n, IterReco
         const double dd = mean - c.mean;
         chi.add(dd * dd / var);
       }
-      chi = wave_merge(chi);
+      chi = wave_merge(chi, lanes);
       c.chi2_dof = chi.value() / (double)(used - 1);
     }
   }
@@ -248,57 +268,92 @@ __device__ inline void finalize_record(double s1, double s2, int64_t n, IterReco
   }
 }
 
+// Inclusive scan over the 64 lanes of a wave, in a fixed order: within the
+// rows of 16 lanes by shifts of 1, 2, 4, 8, then across the rows (DPP).
+__device__ __forceinline__ double wave_scan(double v) {
+  v += dpp_get<0x111>(v);  // row_shr:1
+  v += dpp_get<0x112>(v);
+  v += dpp_get<0x114>(v);
+  v += dpp_get<0x118>(v);
+  // row_bcast15 into rows 1 and 3, row_bcast31 into rows 2 and 3
+  auto bcast = [&](auto ctrl, auto rows) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), decltype(ctrl)::value, decltype(rows)::value, 0xF,
+                                               false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), decltype(ctrl)::value, decltype(rows)::value, 0xF,
+                                               false);
+    v += __hiloint2double(hi, lo);
+  };
+  bcast(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});
+  bcast(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});
+  return v;
+}
+__device__ __forceinline__ double last_lane(double v) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                          __builtin_amdgcn_readlane(__double2loint(v), 63));
+}
+
 // Lepage's refinement of one dimension, by one 64-thread workgroup:
 // 3-point smoothing of the accumulated (f J)^2 per bin, normalisation to
 // p_i, damping r_i = ((1 - p_i)/ln(1/p_i))^alpha, re-binning to equal shares
 // of sum r with r spread uniformly inside each old bin.  A dimension whose
 // histogram is all zero, or not finite (an iteration with a non-finite
 // weight, which the combination excludes too), is left unchanged.
+//
+// Bound by latency: one wave, a chain of dependent steps between two kernels
+// of an iteration.  Lane l holds the bins [l C, l C + C), C = ceil(nb/64), in
+// registers; sums and the cumulative r are wave scans (three serial loops
+// of one thread over the bins took most of the 5.4 us that the kernel had for
+// 50 bins).
 __device__ inline void refine_dim(double* __restrict__ ej, const double* __restrict__ hj, int nb, double alpha) {
   __shared__ double d[VGX_MAX_BINS], r[VGX_MAX_BINS], cum[VGX_MAX_BINS + 1], e[VGX_MAX_BINS + 1];
-  __shared__ double tot_d, tot_sm;
-  for (int i = threadIdx.x; i < nb; i += 64) d[i] = hj[i];
-  for (int i = threadIdx.x; i <= nb; i += 64) e[i] = ej[i];
+  constexpr int CMAX = VGX_MAX_BINS / 64;
+  const int lane = threadIdx.x & 63;
+  const int C = (nb + 63) >> 6, i0 = lane * C;
+  for (int i = lane; i < nb; i += 64) d[i] = hj[i];
+  for (int i = lane; i <= nb; i += 64) e[i] = ej[i];
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int i = 0; i < nb; ++i) s += d[i];
-    tot_d = s;
+  double sm[CMAX];
+  double sd = 0.0, ss = 0.0;
+#pragma unroll
+  for (int c = 0; c < CMAX; ++c) {
+    const int i = i0 + c;
+    sm[c] = 0.0;
+    if (c < C && i < nb) {
+      const double di = d[i], dl = d[i > 0 ? i - 1 : 0], dr = d[i < nb - 1 ? i + 1 : nb - 1];
+      sm[c] = i == 0 ? 0.5 * (di + dr) : i == nb - 1 ? 0.5 * (dl + di) : (dl + di + dr) / 3.0;
+      sd += di;
+      ss += sm[c];
+    }
   }
-  __syncthreads();
+  const double tot_d = last_lane(wave_scan(sd)), tot_sm = last_lane(wave_scan(ss));
   if (!(tot_d > 0.0) || !isfinite(tot_d)) return;  // uniform decision: every thread returns
-  for (int i = threadIdx.x; i < nb; i += 64) {
-    double sm;
-    if (nb == 1) sm = d[0];
-    else if (i == 0) sm = 0.5 * (d[0] + d[1]);
-    else if (i == nb - 1) sm = 0.5 * (d[nb - 2] + d[nb - 1]);
-    else sm = (d[i - 1] + d[i] + d[i + 1]) / 3.0;
-    r[i] = sm;
+  double run = 0.0;
+  double rv[CMAX];
+#pragma unroll
+  for (int c = 0; c < CMAX; ++c) {
+    rv[c] = 0.0;
+    if (c < C && i0 + c < nb) {
+      const double p = sm[c] / tot_sm;
+      if (p > 0.0) {
+        const double q = p >= 1.0 ? 1.0 : (1.0 - p) / -log(p);
+        rv[c] = alpha == 1.5 ? q * sqrt(q) : pow(q, alpha);
+      }
+      run += rv[c];
+    }
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int i = 0; i < nb; ++i) s += r[i];
-    tot_sm = s;
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < nb; i += 64) {
-    const double p = r[i] / tot_sm;
-    double v;
-    if (p <= 0.0) v = 0.0;
-    else if (p >= 1.0) v = 1.0;
-    else v = pow((1.0 - p) / log(1.0 / p), alpha);
-    r[i] = v;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double s = 0.0;
-    cum[0] = 0.0;
-    for (int i = 0; i < nb; ++i) { s += r[i]; cum[i + 1] = s; }
-  }
+  const double incl = wave_scan(run);
+  double acc = __shfl_up(incl, 1, 64);  // the bins before this lane's
+  if (lane == 0) acc = cum[0] = 0.0;
+#pragma unroll
+  for (int c = 0; c < CMAX; ++c)
+    if (c < C && i0 + c < nb) {
+      acc += rv[c];
+      r[i0 + c] = rv[c];
+      cum[i0 + c + 1] = c + 1 == C ? incl : acc;
+    }
   __syncthreads();
   const double step = cum[nb] / (double)nb;
-  for (int k = 1 + threadIdx.x; k < nb; k += 64) {
+  for (int k = 1 + lane; k < nb; k += 64) {
     const double target = (double)k * step;
     // smallest i in [0, nb-1) with cum[i+1] >= target, else nb-1
     int lo = 0, hi = nb - 1;
