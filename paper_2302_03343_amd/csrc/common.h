@@ -122,11 +122,57 @@ __device__ __forceinline__ void copy16(void* dst, const void* src, int bytes) {
   for (; k < n; k += blockDim.x) d[k] = s[k];
 }
 
-// Wave (64-lane) sum of a double using cross-lane shuffles; lane 0 holds it.
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+// The value of another lane by a DPP control word (a few cycles, where a
+// shuffle goes through the LDS); lanes without a source read zero.
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ double dpp_get(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;            // quad_perm [1,0,3,2], [2,3,0,1]
+constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;  // lane i <- 7 - i of 8, 15 - i of 16
+constexpr int kDppXor8 = 0x128;                            // row_ror:8
+
+// Inclusive scan over the 64 lanes of a wave, in a fixed order: within the
+// rows of 16 lanes by shifts of 1, 2, 4, 8, then across the rows.
+__device__ __forceinline__ double wave_scan(double v) {
+  v += dpp_get<0x111>(v);  // row_shr:1
+  v += dpp_get<0x112>(v);
+  v += dpp_get<0x114>(v);
+  v += dpp_get<0x118>(v);
+  v += dpp_get<0x142, 0xA>(v);  // row_bcast15 into rows 1 and 3
+  v += dpp_get<0x143, 0xC>(v);  // row_bcast31 into rows 2 and 3
   return v;
+}
+__device__ __forceinline__ double first_lane(double v) {
+  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                          __builtin_amdgcn_readfirstlane(__double2loint(v)));
+}
+__device__ __forceinline__ double last_lane(double v) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                          __builtin_amdgcn_readlane(__double2loint(v), 63));
+}
+
+// Wave (64-lane) sum of a double, in every lane.
+__device__ __forceinline__ double wave_sum(double v) { return last_lane(wave_scan(v)); }
+
+// The values of rows of 16 lanes (DIST 16) or halves (DIST 32) paired up: a
+// is the lower partner's value and b the upper's, in both.
+template <int DIST>
+__device__ __forceinline__ void lane_pair(double v, double& a, double& b) {
+  const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+  if constexpr (DIST == 16) {
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    a = __hiloint2double((int)h[0], (int)l[0]);
+    b = __hiloint2double((int)h[1], (int)l[1]);
+  } else {
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    a = __hiloint2double((int)h[0], (int)l[0]);
+    b = __hiloint2double((int)h[1], (int)l[1]);
+  }
 }
 
 }  // namespace vgx

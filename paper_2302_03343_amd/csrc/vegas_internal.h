@@ -11,8 +11,6 @@
 #include "singletop.h"
 #include "ttbar_dyn.h"
 
-#include <type_traits>
-
 namespace vgx {
 
 struct IterRecord {
@@ -143,16 +141,16 @@ __device__ __forceinline__ double grid_map_t(const double (&t)[D], const double*
   return jw * nbD;
 }
 
-// The value of another lane by a DPP control word (a few cycles, where a
-// shuffle goes through the LDS); lanes without a source read zero.
-template <int CTRL>
-__device__ __forceinline__ double dpp_get(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
-  return __hiloint2double(hi, lo);
+// Compensated sums of paired rows or halves of a wave, the lower one first.
+template <int DIST>
+__device__ __forceinline__ Comp pair_merge(Comp v) {
+  Comp a, b;
+  lane_pair<DIST>(v.s, a.s, b.s);
+  lane_pair<DIST>(v.c, a.c, b.c);
+  a.add(b.s);
+  a.c += b.c;
+  return a;
 }
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;              // quad_perm [1,0,3,2], [2,3,0,1]
-constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;    // lane i <- 7 - i of 8, 15 - i of 16
 
 // Merge of compensated sums over the first `lanes` lanes of a wave (the
 // others hold zeros) into lane 0, in a fixed order: pairs, quads, eights,
@@ -167,14 +165,9 @@ __device__ __forceinline__ Comp wave_merge(Comp a, int lanes) {
   if (lanes > 2) level(dpp_get<kDppXor2>(a.s), dpp_get<kDppXor2>(a.c));
   if (lanes > 4) level(dpp_get<kDppHalfMirror>(a.s), dpp_get<kDppHalfMirror>(a.c));
   if (lanes > 8) level(dpp_get<kDppMirror>(a.s), dpp_get<kDppMirror>(a.c));
-  if (lanes > 16) level(__shfl_xor(a.s, 16, 64), __shfl_xor(a.c, 16, 64));
-  if (lanes > 32) level(__shfl_xor(a.s, 32, 64), __shfl_xor(a.c, 32, 64));
+  if (lanes > 16) a = pair_merge<16>(a);
+  if (lanes > 32) a = pair_merge<32>(a);
   return a;
-}
-
-__device__ __forceinline__ double first_lane(double v) {
-  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
-                          __builtin_amdgcn_readfirstlane(__double2loint(v)));
 }
 
 // Estimate of one iteration from its compensated sums, stored as record
@@ -266,30 +259,6 @@ __device__ inline void finalize_record(double s1, double s2, int64_t n, IterReco
       __hip_atomic_store(host.flag, host.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
   }
-}
-
-// Inclusive scan over the 64 lanes of a wave, in a fixed order: within the
-// rows of 16 lanes by shifts of 1, 2, 4, 8, then across the rows (DPP).
-__device__ __forceinline__ double wave_scan(double v) {
-  v += dpp_get<0x111>(v);  // row_shr:1
-  v += dpp_get<0x112>(v);
-  v += dpp_get<0x114>(v);
-  v += dpp_get<0x118>(v);
-  // row_bcast15 into rows 1 and 3, row_bcast31 into rows 2 and 3
-  auto bcast = [&](auto ctrl, auto rows) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), decltype(ctrl)::value, decltype(rows)::value, 0xF,
-                                               false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), decltype(ctrl)::value, decltype(rows)::value, 0xF,
-                                               false);
-    v += __hiloint2double(hi, lo);
-  };
-  bcast(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});
-  bcast(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});
-  return v;
-}
-__device__ __forceinline__ double last_lane(double v) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
-                          __builtin_amdgcn_readlane(__double2loint(v), 63));
 }
 
 // Lepage's refinement of one dimension, by one 64-thread workgroup:
