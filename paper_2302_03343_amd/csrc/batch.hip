@@ -13,8 +13,8 @@
 //     range [tile0_i, tile0_i + ntiles_i);
 //   * a persistent grid (as many workgroups as can be resident at once)
 //     pops tile indices from an atomic counter, so integrals with 1e4 and
-//     1e7 samples load-balance across the 256 CUs; a workgroup re-stages the
-//     grid edges in LDS only when the integral changes between its tiles;
+//     1e7 samples load-balance across the 256 CUs; the grid's bins are read
+//     from global memory (L1), so nothing is staged per tile;
 //   * the tile's histogram is kept in up to four LDS copies (lane l adds into
 //     copy l mod copies) and summed in copy order;
 //   * every tile writes its own partial row (S1, S2 compensated, histogram),
@@ -42,7 +42,7 @@ namespace vgx {
 
 constexpr int BB_MAX = 256;  // launch bound of the persistent kernel
 // Copies of a tile's LDS histogram (1, 2 or 4 per batch, as many as fit in
-// kCopiesLds with the edges): lane l adds into copy l mod copies, so lanes of
+// kCopiesLds): lane l adds into copy l mod copies, so lanes of
 // one atomic instruction that fall into the same bin mostly hit different
 // addresses (LDS atomics on one address serialise); a copy is D nb + 1
 // doubles so that a bin's copies fall on different banks.  The copies are
@@ -51,7 +51,7 @@ constexpr int kMaxHistCopies = 4;
 constexpr size_t kCopiesLds = 48 * 1024;
 __host__ __device__ inline int hist_stride(int dim, int nb) { return dim * nb + 1; }
 __host__ __device__ inline size_t batch_lds_bytes(int dim, int nb, int copies) {
-  return sizeof(double) * ((size_t)dim * (nb + 1) + (size_t)copies * hist_stride(dim, nb));
+  return sizeof(double) * (size_t)copies * hist_stride(dim, nb);
 }
 
 struct BatchItem {
@@ -64,6 +64,7 @@ struct BatchItem {
   int64_t part_off;      // first double of this integral's tile partials
   double alpha;
   double* edges;         // context grid [dim][nb+1]
+  double2* bins;         // and its bins [dim][nb]
   double* hist;          // context histogram [dim][nb]
   IterRecord* rec;       // context records
   Combined* comb;
@@ -80,17 +81,15 @@ struct BatchState {
 __host__ __device__ inline int* batch_krec(BatchState* st) { return (int*)(st + 1); }
 
 template <int D, class F>
-__device__ __forceinline__ void run_tile(const BatchItem& it, const F& f, const double* se, double* sh, int64_t s0,
-                                         int64_t s1, uint32_t iter, Comp& c1, Comp& c2) {
+__device__ __forceinline__ void run_tile(const BatchItem& it, const F& f, double* sh, int64_t s0, int64_t s1,
+                                         uint32_t iter, Comp& c1, Comp& c2) {
   double p1 = 0.0, p2 = 0.0;
-  // scaled coordinates t = u N straight from the Philox words (exact), the
-  // Jacobian's constant N^D
-  const double nbd = (double)it.nb, sc = nbd * 0x1p-32, hf = nbd * 0x1p-33;
-  double nbD = 1.0;
+  double nbDs = 1.0;
 #pragma unroll
-  for (int j = 0; j < D; ++j) nbD *= nbd;
+  for (int j = 0; j < D; ++j) nbDs *= (double)it.nb * 0x1p32;
   for (int64_t i = s0 + threadIdx.x; i < s1; i += blockDim.x) {
-    double t[D], x[D];
+    double x[D];
+    uint32_t k[D];
     int idx[D];
 #pragma unroll
     for (int b = 0; b < (D + 3) / 4; ++b) {
@@ -99,11 +98,10 @@ __device__ __forceinline__ void run_tile(const BatchItem& it, const F& f, const 
       const uint32_t ww[4] = {w4.x, w4.y, w4.z, w4.w};
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        if (4 * b + e < D) t[4 * b + e < D ? 4 * b + e : 0] = fma((double)ww[e], sc, hf);
+        if (4 * b + e < D) k[4 * b + e < D ? 4 * b + e : 0] = ww[e];
     }
-    // edge pairs from global memory: the LDS holds the histogram copies
-    const double jac = grid_map_t<D, true, true>(t, se, it.edges, it.nb, nbD, x, idx);
-    const double w = f.eval(x) * jac;
+    const double jac = grid_map_words<D>(k, it.bins, it.nb, nbDs, x, idx);
+    const double w = eval_inside(f, x) * jac;
     const double w2 = w * w;
     p1 += w;
     p2 += w2;
@@ -115,17 +113,17 @@ __device__ __forceinline__ void run_tile(const BatchItem& it, const F& f, const 
 }
 
 template <int D>
-__device__ __forceinline__ void run_tile_d(const BatchItem& it, const double* se, double* sh, int64_t s0, int64_t s1,
-                                           uint32_t iter, Comp& c1, Comp& c2) {
+__device__ __forceinline__ void run_tile_d(const BatchItem& it, double* sh, int64_t s0, int64_t s1, uint32_t iter,
+                                           Comp& c1, Comp& c2) {
 #define VGX_BT(T)                                                      \
   if (it.prec == VGX_F64) {                                            \
     T<D, double> f;                                                    \
     f.prm = it.prm;                                                    \
-    run_tile<D>(it, f, se, sh, s0, s1, iter, c1, c2);                  \
+    run_tile<D>(it, f, sh, s0, s1, iter, c1, c2);                  \
   } else {                                                             \
     T<D, float> f;                                                     \
     f.prm = it.prm;                                                    \
-    run_tile<D>(it, f, se, sh, s0, s1, iter, c1, c2);                  \
+    run_tile<D>(it, f, sh, s0, s1, iter, c1, c2);                  \
   }
   switch (it.kind) {
     case VGX_GAUSS: { VGX_BT(Gauss) break; }
@@ -148,9 +146,7 @@ __global__ __launch_bounds__(BB_MAX) void k_batch(const BatchItem* __restrict__ 
   __shared__ int s_item;
   __shared__ double red[4][BB_MAX / 64];
   const uint32_t iter = (uint32_t)st->iteration;
-  int cur = -1;
-  double* se = lds;  // edges of the current integral [dim][nb+1]
-  double* sh = nullptr;
+  double* sh = lds;
   while (true) {
     if (threadIdx.x == 0) {
       const int64_t t = (int64_t)atomicAdd(&st->tile_counter, 1ull);
@@ -167,12 +163,6 @@ __global__ __launch_bounds__(BB_MAX) void k_batch(const BatchItem* __restrict__ 
     if (t >= total_tiles) break;  // uniform: every wave leaves
     const int k = s_item;
     const BatchItem& it = items[k];
-    const int ne = it.dim * (it.nb + 1);
-    if (k != cur) {
-      for (int q = threadIdx.x; q < ne; q += blockDim.x) se[q] = it.edges[q];
-      cur = k;
-    }
-    sh = se + ne;
     const int hs = hist_stride(it.dim, it.nb);
     for (int q = threadIdx.x; q < copies * hs; q += blockDim.x) sh[q] = 0.0;
     __syncthreads();
@@ -182,18 +172,18 @@ __global__ __launch_bounds__(BB_MAX) void k_batch(const BatchItem* __restrict__ 
     Comp c1, c2;
     double* shl = sh + (threadIdx.x & (copies - 1)) * hs;  // this lane's histogram copy
     switch (it.dim) {
-      case 1: run_tile_d<1>(it, se, shl, s0, s1, iter, c1, c2); break;
-      case 2: run_tile_d<2>(it, se, shl, s0, s1, iter, c1, c2); break;
-      case 3: run_tile_d<3>(it, se, shl, s0, s1, iter, c1, c2); break;
-      case 4: run_tile_d<4>(it, se, shl, s0, s1, iter, c1, c2); break;
-      case 5: run_tile_d<5>(it, se, shl, s0, s1, iter, c1, c2); break;
-      case 6: run_tile_d<6>(it, se, shl, s0, s1, iter, c1, c2); break;
-      case 7: run_tile_d<7>(it, se, shl, s0, s1, iter, c1, c2); break;
-      case 8: run_tile_d<8>(it, se, shl, s0, s1, iter, c1, c2); break;
-      case 9: run_tile_d<9>(it, se, shl, s0, s1, iter, c1, c2); break;
-      case 10: run_tile_d<10>(it, se, shl, s0, s1, iter, c1, c2); break;
-      case 11: run_tile_d<11>(it, se, shl, s0, s1, iter, c1, c2); break;
-      default: run_tile_d<12>(it, se, shl, s0, s1, iter, c1, c2); break;
+      case 1: run_tile_d<1>(it, shl, s0, s1, iter, c1, c2); break;
+      case 2: run_tile_d<2>(it, shl, s0, s1, iter, c1, c2); break;
+      case 3: run_tile_d<3>(it, shl, s0, s1, iter, c1, c2); break;
+      case 4: run_tile_d<4>(it, shl, s0, s1, iter, c1, c2); break;
+      case 5: run_tile_d<5>(it, shl, s0, s1, iter, c1, c2); break;
+      case 6: run_tile_d<6>(it, shl, s0, s1, iter, c1, c2); break;
+      case 7: run_tile_d<7>(it, shl, s0, s1, iter, c1, c2); break;
+      case 8: run_tile_d<8>(it, shl, s0, s1, iter, c1, c2); break;
+      case 9: run_tile_d<9>(it, shl, s0, s1, iter, c1, c2); break;
+      case 10: run_tile_d<10>(it, shl, s0, s1, iter, c1, c2); break;
+      case 11: run_tile_d<11>(it, shl, s0, s1, iter, c1, c2); break;
+      default: run_tile_d<12>(it, shl, s0, s1, iter, c1, c2); break;
     }
     const double v0 = wave_sum(c1.s), v1 = wave_sum(c1.c), v2 = wave_sum(c2.s), v3 = wave_sum(c2.c);
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
@@ -268,7 +258,8 @@ __global__ __launch_bounds__(BR_GROUPS * BR_COLS) void k_batch_reduce(const Batc
 __global__ __launch_bounds__(64) void k_batch_refine(const BatchItem* __restrict__ items, BatchState* st) {
   const BatchItem& it = items[blockIdx.y];
   if ((int)blockIdx.x >= it.dim) return;  // uniform per block
-  refine_dim(it.edges + (size_t)blockIdx.x * (it.nb + 1), it.hist + (size_t)blockIdx.x * it.nb, it.nb, it.alpha);
+  refine_dim(it.edges + (size_t)blockIdx.x * (it.nb + 1), it.bins + (size_t)blockIdx.x * it.nb,
+             it.hist + (size_t)blockIdx.x * it.nb, it.nb, it.alpha);
 }
 
 }  // namespace vgx
@@ -435,6 +426,7 @@ extern "C" vgx_status batch_create(vgx_vegas* const* ctxs, int32_t count, const 
     it.n = n_samples[k];
     it.alpha = c->alpha;
     it.edges = c->edges;
+    it.bins = c->bins;
     it.hist = c->hist;
     it.rec = c->rec;
     it.comb = c->comb;

@@ -49,11 +49,11 @@ constexpr int CHUNK = 16;
 struct VegasArgs {
   int64_t n;
   const double* edges;
+  const double2* bins;  // grid_bin per dimension and bin
   int nb;
   int pstride;   // doubles per workgroup partial row
   int hcopies;   // histogram copies in LDS: 4 per wave, one per wave, or 1 (shared)
-  double nbD;    // nb^dim, the Jacobian's constant factor
-  double sc;     // nb 2^-32: t = u nb = (word + 1/2) sc
+  double nbD;    // nb^dim, the Jacobian's constant factor (Philox kernels: (nb 2^32)^dim)
   // the integrand's LDS tables as staged once for the context (copied by
   // each workgroup), or null (each workgroup stages them itself)
   const float* tables;
@@ -78,29 +78,11 @@ __host__ __device__ inline int hist_copies(int D, int nb, bool lane_groups) {
 // ---------------------------------------------------------------------------
 template <int D>
 struct PhiloxSrc {
-  static constexpr bool kInterior = true;  // 0 < u N < N for every sample
+  static constexpr bool kInterior = true;  // Philox words, inside the cube
   uint32_t it, sid, k0, k1;
   int64_t first;
   __device__ __forceinline__ double get(int64_t i, double (&u)[D]) const {
     philox_uniforms<D>((uint64_t)(first + i), it, sid, k0, k1, u);
-    return 1.0;
-  }
-  // scaled coordinates t = u N = (k + 1/2) N 2^-32 of counter (c0, c1), exact
-  // (k N 2^-32 has at most 40 significant bits): one FMA with the two
-  // constants in registers, or (LEAN, for register-bound kernels) k + 1/2
-  // (an inline constant) times the uniform scale, two instructions and no
-  // vector registers for the constants
-  template <bool LEAN>
-  __device__ __forceinline__ double get_t_c(uint32_t c0, uint32_t c1, double sc, double hf, double (&t)[D]) const {
-#pragma unroll
-    for (int b = 0; b < (D + 3) / 4; ++b) {
-      const u32x4 w = philox4x32_10(c0, c1, it, (sid << 8) | (uint32_t)b, k0, k1);
-      const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (4 * b + e < D)
-          t[4 * b + e < D ? 4 * b + e : 0] = LEAN ? ((double)ww[e] + 0.5) * sc : fma((double)ww[e], sc, hf);
-    }
     return 1.0;
   }
   // Samples are taken in segments within which the low counter word does
@@ -110,11 +92,17 @@ struct PhiloxSrc {
     const int64_t room = ((int64_t)1 << 31) - (int64_t)((uint64_t)(first + base) & 0x7FFFFFFFu);
     return left < room ? left : room;
   }
-  template <bool LEAN>
-  __device__ __forceinline__ double get_t_seg(int64_t base, uint32_t i, double nbd, double sc, double hf,
-                                              double (&t)[D]) const {
+  // the words of sample base + i
+  __device__ __forceinline__ void words(int64_t base, uint32_t i, uint32_t (&k)[D]) const {
     const uint64_t c = (uint64_t)(first + base);
-    return get_t_c<LEAN>((uint32_t)c + i, (uint32_t)(c >> 32), sc, hf, t);
+#pragma unroll
+    for (int b = 0; b < (D + 3) / 4; ++b) {
+      const u32x4 w = philox4x32_10((uint32_t)c + i, (uint32_t)(c >> 32), it, (sid << 8) | (uint32_t)b, k0, k1);
+      const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (4 * b + e < D) k[4 * b + e < D ? 4 * b + e : 0] = ww[e];
+    }
   }
 };
 
@@ -132,9 +120,8 @@ struct PointsSrc {
   __host__ __device__ __forceinline__ int64_t seg_len(int64_t base, int64_t left) const {
     return left < ((int64_t)1 << 31) ? left : ((int64_t)1 << 31);
   }
-  template <bool LEAN>
-  __device__ __forceinline__ double get_t_seg(int64_t base, uint32_t i32, double nbd, double sc, double hf,
-                                              double (&t)[D]) const {
+  // the scaled coordinates t = u N of point base + i and its weight 1/q
+  __device__ __forceinline__ double scaled(int64_t base, uint32_t i32, double nbd, double (&t)[D]) const {
     const int64_t i = base + i32;
 #pragma unroll
     for (int j = 0; j < D; ++j) t[j] = y[(int64_t)j * n + i] * nbd;
@@ -142,10 +129,12 @@ struct PointsSrc {
   }
 };
 
-// Offset (in doubles, even: 16-byte aligned) of the integrand tables after
-// the edges [D][nb+1] and, with histograms, [copies][D][nb].
-__host__ __device__ inline int lds_table_offset(int D, int nb, bool hist, bool lane_groups) {
-  const int n = D * (nb + 1) + (hist ? hist_copies(D, nb, lane_groups) * D * nb : 0);
+// Offset (in doubles, even: 16-byte aligned) of the integrand tables in LDS:
+// after the edges [D][nb+1] (caller points with tables, vegas_sample; other
+// kernels read the grid from global memory) and, with histograms,
+// [copies][D][nb].
+__host__ __device__ inline int lds_table_offset(bool edges, int D, int nb, bool hist, bool lane_groups) {
+  const int n = (edges ? D * (nb + 1) : 0) + (hist ? hist_copies(D, nb, lane_groups) * D * nb : 0);
   return (n + 1) & ~1;
 }
 
@@ -178,7 +167,8 @@ __device__ __forceinline__ void stage_tables(F& ff, float* extra, const VegasArg
 
 // ---------------------------------------------------------------------------
 // Fused iteration kernel.
-// LDS: edges [D][nb+1] | histogram [D][nb] (HIST) | integrand staging.
+// LDS: edges [D][nb+1] (caller points, integrands with tables) | histogram
+// copies [D][nb] (HIST) | integrand staging.
 // Partial row per workgroup: [S1.s, S1.c, S2.s, S2.c, hist[D][nb]].
 // ---------------------------------------------------------------------------
 // Minimum waves per SIMD an integrand asks of the iteration kernel (its
@@ -195,12 +185,14 @@ template <int D, class F, class Src, bool HIST, bool WIDE = false>
 __global__ __launch_bounds__(BLOCK, Src::kInterior ? MinWaves<F>::value : 1) void k_vegas_iter(VegasArgs a, F f, Src src,
                                                                           double* __restrict__ partials) {
   extern __shared__ __align__(16) double lds[];
+  constexpr bool EDGES = !Src::kInterior && F::kStage;
   const int nb = a.nb;
   double* se = lds;
-  double* sh = se + D * (nb + 1);
+  double* sh = se + (EDGES ? D * (nb + 1) : 0);
   // integrand tables start on a 16-byte boundary (they are read as float4)
-  float* extra = (float*)(lds + lds_table_offset(D, nb, HIST, !F::kStage));
-  for (int k = threadIdx.x; k < D * (nb + 1); k += BLOCK) se[k] = a.edges[k];
+  float* extra = (float*)(lds + lds_table_offset(EDGES, D, nb, HIST, !F::kStage));
+  if (EDGES)
+    for (int k = threadIdx.x; k < D * (nb + 1); k += BLOCK) se[k] = a.edges[k];
   if (HIST)
     for (int k = threadIdx.x; k < a.hcopies * D * nb; k += BLOCK) sh[k] = 0.0;
   F ff = f;
@@ -222,14 +214,21 @@ __global__ __launch_bounds__(BLOCK, Src::kInterior ? MinWaves<F>::value : 1) voi
 
   Comp c1, c2;
   double p1 = 0.0, p2 = 0.0;
-  const double nbd = (double)nb, sc = a.sc, hf = nbd * 0x1p-33;
-  // one sample from its scaled coordinates and source weight
-  auto sample = [&](const double (&t)[D], double ws) {
-    double x[D];
+  // one sample
+  auto sample = [&](int64_t base, uint32_t i) {
+    double x[D], w;
     int idx[D];
-    // integrands without LDS tables: the edge pairs come from global memory
-    const double jac = grid_map_t<D, Src::kInterior, !F::kStage>(t, se, a.edges, nb, a.nbD, x, idx);
-    const double w = ff.eval(x) * jac * ws;
+    if constexpr (Src::kInterior) {
+      uint32_t k[D];
+      src.words(base, i, k);
+      const double jac = grid_map_words<D>(k, a.bins, nb, a.nbD, x, idx);
+      w = eval_inside(ff, x) * jac;
+    } else {
+      double t[D];
+      const double ws = src.scaled(base, i, (double)nb, t);
+      const double jac = grid_map_t<D, !F::kStage>(t, se, a.edges, nb, a.nbD, x, idx);
+      w = ff.eval(x) * jac * ws;
+    }
     const double w2 = w * w;
     p1 += w;
     p2 += w2;
@@ -246,10 +245,7 @@ __global__ __launch_bounds__(BLOCK, Src::kInterior ? MinWaves<F>::value : 1) voi
   int cnt = 0;
   auto run = [&](int64_t base, uint32_t len) {
     for (uint32_t i = blockIdx.x * BLOCK + threadIdx.x; i < len; i += stride) {
-      double t[D];
-      // integrands with LDS tables are register-bound (occupancy)
-      const double ws = src.template get_t_seg<F::kStage>(base, i, nbd, sc, hf, t);
-      sample(t, ws);
+      sample(base, i);
       if (++cnt == CHUNK) {
         c1.add(p1);
         c2.add(p2);
@@ -317,13 +313,14 @@ __global__ __launch_bounds__(FI_BLOCK) void k_flow_iter(VegasArgs a, F f, FlowIt
   extern __shared__ __align__(16) double lds[];
   const int nb = a.nb;
   double* se = lds;
-  float* extra = (float*)(lds + lds_table_offset(D, nb, false, !F::kStage));
+  float* extra = (float*)(lds + lds_table_offset(F::kStage, D, nb, false, !F::kStage));
   unsigned char* fl = (unsigned char*)lds + fa.flow_off;
   const FlowDesc& FD = *fa.desc;
   S* sfw = (S*)fl;
   float* sb = (float*)(fl + (size_t)FD.fw_total * sizeof(S));
   float* z = (float*)(fl + fwd_z_offset(FD.fw_total, FD.bias_total, (int)sizeof(S))) + threadIdx.x;
-  for (int k = threadIdx.x; k < D * (nb + 1); k += FI_BLOCK) se[k] = a.edges[k];
+  if (F::kStage)
+    for (int k = threadIdx.x; k < D * (nb + 1); k += FI_BLOCK) se[k] = a.edges[k];
   F ff = f;
   if constexpr (F::kStage) stage_tables(ff, extra, a);
   copy16(sfw, fa.fw, FD.fw_total * (int)sizeof(S));
@@ -347,7 +344,7 @@ __global__ __launch_bounds__(FI_BLOCK) void k_flow_iter(VegasArgs a, F f, FlowIt
       int idx[D];
 #pragma unroll
       for (int j = 0; j < D; ++j) tt[j] = (double)z[j * FI_BLOCK] * nbd;
-      const double jac = grid_map_t<D, false, !F::kStage>(tt, se, a.edges, nb, a.nbD, x, idx);
+      const double jac = grid_map_t<D, !F::kStage>(tt, se, a.edges, nb, a.nbD, x, idx);
       const double w = ff.eval(x) * jac * exp(-lq);
       p1 += w;
       p2 += w * w;
@@ -455,14 +452,16 @@ __global__ __launch_bounds__(RBLOCK) void k_reduce(const double* __restrict__ pa
 // Refinement, one workgroup per dimension; with k_pend >= 0 the grid has one
 // more workgroup, which completes the deferred record k_pend of n_pend
 // samples from the S1 and S2 stored in it (the refinement does not read it).
-__global__ __launch_bounds__(64) void k_refine(double* __restrict__ edges, const double* __restrict__ hist, int nb,
-                                               double alpha, IterRecord* __restrict__ rec, int k_pend, int64_t n_pend,
+__global__ __launch_bounds__(64) void k_refine(double* __restrict__ edges, double2* __restrict__ bins,
+                                               const double* __restrict__ hist, int nb, double alpha,
+                                               IterRecord* __restrict__ rec, int k_pend, int64_t n_pend,
                                                Combined* __restrict__ comb) {
   if (k_pend >= 0 && blockIdx.x == gridDim.x - 1) {
     finalize_record(rec[k_pend].s1, rec[k_pend].s2, n_pend, rec, k_pend, comb);
     return;
   }
-  refine_dim(edges + (size_t)blockIdx.x * (nb + 1), hist + (size_t)blockIdx.x * nb, nb, alpha);
+  refine_dim(edges + (size_t)blockIdx.x * (nb + 1), bins + (size_t)blockIdx.x * nb, hist + (size_t)blockIdx.x * nb, nb,
+             alpha);
 }
 
 __global__ __launch_bounds__(64) void k_finalize(IterRecord* __restrict__ rec, int k, int64_t n,
@@ -479,7 +478,7 @@ __global__ __launch_bounds__(BLOCK) void k_vegas_sample(VegasArgs a, F f, Philox
   extern __shared__ __align__(16) double lds[];
   const int nb = a.nb;
   double* se = lds;
-  float* extra = (float*)(lds + lds_table_offset(D, nb, false, !F::kStage));
+  float* extra = (float*)(lds + lds_table_offset(true, D, nb, false, !F::kStage));
   for (int k = threadIdx.x; k < D * (nb + 1); k += BLOCK) se[k] = a.edges[k];
   F ff = f;
   if constexpr (F::kStage) stage_tables(ff, extra, a);
@@ -522,7 +521,7 @@ size_t extra_lds_bytes(const vgx_vegas* v) {
 // fills the chip.
 int hadronic_blocks_per_cu(const vgx_vegas* v) {
   int occ = 0;
-  const size_t lds = sizeof(double) * (size_t)lds_table_offset(3, v->nb, true, false) + extra_lds_bytes(v);
+  const size_t lds = sizeof(double) * (size_t)lds_table_offset(false, 3, v->nb, true, false) + extra_lds_bytes(v);
   const void* k = (v->kind == VGX_TTBAR && v->tt_dyn)
                       ? reinterpret_cast<const void*>(&k_vegas_iter<3, TTbarDyn, PhiloxSrc<3>, true>)
                   : v->kind == VGX_TTBAR    ? reinterpret_cast<const void*>(&k_vegas_iter<3, TTbar, PhiloxSrc<3>, true>)
@@ -732,6 +731,9 @@ vgx_status prepare_params(vgx_vegas* v, const vgx_vegas_cfg* c) {
         norm *= 1.0 / (s * sqrt(2.0 * M_PI));
       }
       p[2 * d] = norm;
+      for (int j = 0; j < d; ++j)
+        // the kernels' exponential takes no NaN: a z = x k - c k that is one makes the norm one
+        if (isnan(p[d + j] - p[j] * p[d + j])) p[2 * d] = NAN;
       return VGX_OK;
     }
     case VGX_GENZ_OSC:
@@ -848,14 +850,16 @@ constexpr int kFewSamples = 4;
 // Launch helpers dispatching on (kind, prec, D).
 template <int D, class F, class Src, bool HIST>
 vgx_status launch_iter_f(vgx_vegas* v, int64_t n, const F& f, const Src& src) {
-  VegasArgs a{n, v->edges, v->nb, v->pstride, hist_copies(D, v->nb, !F::kStage), pow_int((double)v->nb, D),
-              v->nb * 0x1p-32, v->tables, v->table_bytes};
+  VegasArgs a{n, v->edges, v->bins, v->nb, v->pstride, hist_copies(D, v->nb, !F::kStage),
+              pow_int(v->nb * (Src::kInterior ? 0x1p32 : 1.0), D), v->tables, v->table_bytes};
   const int grid = grid_for(v, n);
   // a few samples per thread: clearing and summing sixteen copies costs more
   // than their atomics' conflicts (d = 4, 50 bins: 13.2 -> 12.1 us at 1e6 samples, 8.4 -> 7.5 at 3e5; equal
   // from 2e6 on)
   if (a.hcopies > BLOCK / 64 && n <= (int64_t)grid * BLOCK * kFewSamples) a.hcopies = BLOCK / 64;
-  const size_t lds = sizeof(double) * (size_t)lds_table_offset(D, v->nb, HIST, !F::kStage) + extra_lds_bytes(v);
+  const size_t lds =
+      sizeof(double) * (size_t)lds_table_offset(!Src::kInterior && F::kStage, D, v->nb, HIST, !F::kStage) +
+      extra_lds_bytes(v);
   if (src.seg_len(0, n) == n)  // one segment: the common case
     hipLaunchKernelGGL((k_vegas_iter<D, F, Src, HIST, false>), dim3(grid), dim3(BLOCK), lds, v->stream, a, f, src,
                        v->partials);
@@ -924,11 +928,11 @@ vgx_status launch_iter_d(vgx_vegas* v, int64_t n, const Src& src) {
 
 template <int D, class F>
 vgx_status launch_sample_f(vgx_vegas* v, int64_t first, int64_t n, int32_t it, const F& f, double* u, double* g) {
-  VegasArgs a{n, v->edges, v->nb, v->pstride, hist_copies(D, v->nb, !F::kStage), pow_int((double)v->nb, D),
-              v->nb * 0x1p-32, v->tables, v->table_bytes};
+  VegasArgs a{n, v->edges, v->bins, v->nb, v->pstride, hist_copies(D, v->nb, !F::kStage), pow_int((double)v->nb, D),
+              v->tables, v->table_bytes};
   PhiloxSrc<D> src{(uint32_t)it, v->stream_id, (uint32_t)v->seed, (uint32_t)(v->seed >> 32), first};
   const int grid = grid_for(v, n);
-  const size_t lds = sizeof(double) * (size_t)lds_table_offset(D, v->nb, false, !F::kStage) + extra_lds_bytes(v);
+  const size_t lds = sizeof(double) * (size_t)lds_table_offset(true, D, v->nb, false, !F::kStage) + extra_lds_bytes(v);
   hipLaunchKernelGGL((k_vegas_sample<D, F>), dim3(grid), dim3(BLOCK), lds, v->stream, a, f, src, u, g);
   VGX_HIP(hipGetLastError());
   return VGX_OK;
@@ -1050,9 +1054,9 @@ vgx_status launch_points_iter(vgx_vegas* v, int64_t n, const double* y, const do
 // grid (the partial rows to reduce).
 template <int D, class F>
 vgx_status launch_flow_iter_f(vgx_vegas* v, const FlowView& fv, int64_t n, FlowIterArgs fa, const F& f, int* grid) {
-  VegasArgs a{n, v->edges, v->nb, v->pstride, 1, pow_int((double)v->nb, D), v->nb * 0x1p-32, v->tables,
-              v->table_bytes};
-  const size_t base = sizeof(double) * (size_t)lds_table_offset(D, v->nb, false, !F::kStage) + extra_lds_bytes(v);
+  VegasArgs a{n, v->edges, v->bins, v->nb, v->pstride, 1, pow_int((double)v->nb, D), v->tables, v->table_bytes};
+  const size_t base =
+      sizeof(double) * (size_t)lds_table_offset(F::kStage, D, v->nb, false, !F::kStage) + extra_lds_bytes(v);
   const size_t off = (base + 15) & ~(size_t)15;
   const size_t lds = off + fwd_z_offset(fv.fw_total, fv.bias_total, 2) + sizeof(float) * (size_t)D * FI_BLOCK;
   VGX_CHECK(lds <= 160 * 1024, "flow_vegas_iterate: the flow's weights and the integrand's tables need %zu bytes of LDS",
@@ -1256,6 +1260,18 @@ vgx_status vegas_flush_pending(vgx_vegas* v) {
   return VGX_OK;
 }
 
+// The edges in the pinned memory, with their bins, to the device (async).
+static hipError_t upload_grid(vgx_vegas* v) {
+  double* e = v->host()->grid;
+  double2* b = (double2*)(e + v->edge_doubles());
+  for (int j = 0; j < v->dim; ++j)
+    for (int k = 0; k < v->nb; ++k) {
+      const double* p = e + (size_t)j * (v->nb + 1) + k;
+      b[(size_t)j * v->nb + k] = grid_bin(p[0], p[1], v->nb);
+    }
+  return hipMemcpyAsync(v->edges, e, sizeof(double) * v->grid_doubles(), hipMemcpyHostToDevice, v->stream);
+}
+
 extern "C" vgx_status vegas_create(const vgx_vegas_cfg* c, void* stream, vgx_vegas** out) {
   VGX_CHECK(c && out, "vegas_create: null argument");
   *out = nullptr;
@@ -1281,14 +1297,14 @@ extern "C" vgx_status vegas_create(const vgx_vegas_cfg* c, void* stream, vgx_veg
   v->max_wg = device_cus() * (uses_pdf(c->kind) ? hadronic_blocks_per_cu(v) : 8);
   v->max_wg = v->max_wg < RMAXROWS ? v->max_wg : RMAXROWS;  // rows one reduction takes
   v->pstride = 4 + v->dim * v->nb;
-  const size_t ne = (size_t)v->dim * (v->nb + 1);
   do {
-    if ((s = dev_alloc((void**)&v->edges, sizeof(double) * ne)) != VGX_OK) break;
+    if ((s = dev_alloc((void**)&v->edges, sizeof(double) * v->grid_doubles())) != VGX_OK) break;
+    v->bins = (double2*)(v->edges + v->edge_doubles());
     if ((s = dev_alloc((void**)&v->hist, sizeof(double) * v->dim * v->nb)) != VGX_OK) break;
     if ((s = dev_alloc((void**)&v->partials, sizeof(double) * (size_t)v->max_wg * v->pstride)) != VGX_OK) break;
     if ((s = dev_alloc((void**)&v->rec, sizeof(IterRecord) * MAX_RECORDS)) != VGX_OK) break;
     if ((s = dev_alloc((void**)&v->comb, sizeof(Combined))) != VGX_OK) break;
-    if ((s = host_alloc(&v->pinned, sizeof(PinnedHost) + sizeof(double) * ne)) != VGX_OK) break;
+    if ((s = host_alloc(&v->pinned, sizeof(PinnedHost) + sizeof(double) * v->grid_doubles())) != VGX_OK) break;
     if ((s = build_tables(v)) != VGX_OK) break;
   } while (0);
   if (s != VGX_OK) { vegas_destroy(v); return s; }
@@ -1296,7 +1312,7 @@ extern "C" vgx_status vegas_create(const vgx_vegas_cfg* c, void* stream, vgx_veg
   double* h = v->host()->grid;
   for (int j = 0; j < v->dim; ++j)
     for (int k = 0; k <= v->nb; ++k) h[j * (v->nb + 1) + k] = (double)k / (double)v->nb;
-  hipError_t e = hipMemcpyAsync(v->edges, h, sizeof(double) * ne, hipMemcpyHostToDevice, v->stream);
+  hipError_t e = upload_grid(v);
   if (e == hipSuccess) e = hipMemsetAsync(v->hist, 0, sizeof(double) * v->dim * v->nb, v->stream);
   if (e == hipSuccess) e = hipMemsetAsync(v->comb, 0, sizeof(Combined), v->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(v->stream);
@@ -1336,8 +1352,8 @@ extern "C" vgx_status vegas_refine(vgx_vegas* v) {
   VGX_CHECK(v, "vegas_refine: null context");
   if (!v->have_hist) { set_error("vegas_refine: no histogram (run vegas_iterate first)"); return VGX_ESTATE; }
   const int kp = v->pend_k;
-  hipLaunchKernelGGL(k_refine, dim3(v->dim + (kp >= 0 ? 1 : 0)), dim3(64), 0, v->stream, v->edges, v->hist, v->nb,
-                     v->alpha, v->rec, kp, v->pend_n, v->comb);
+  hipLaunchKernelGGL(k_refine, dim3(v->dim + (kp >= 0 ? 1 : 0)), dim3(64), 0, v->stream, v->edges, v->bins, v->hist,
+                     v->nb, v->alpha, v->rec, kp, v->pend_n, v->comb);
   VGX_HIP(hipGetLastError());
   v->pend_k = -1;
   return VGX_OK;
@@ -1414,7 +1430,7 @@ extern "C" vgx_status vegas_set_grid(vgx_vegas* v, const double* edges) {
   double* h = v->host()->grid;
   VGX_HIP(hipStreamSynchronize(v->stream));  // an earlier copy from h may be under way
   memcpy(h, edges, bytes);
-  VGX_HIP(hipMemcpyAsync(v->edges, h, bytes, hipMemcpyHostToDevice, v->stream));
+  VGX_HIP(upload_grid(v));
   v->tail = true;
   return VGX_OK;
 }

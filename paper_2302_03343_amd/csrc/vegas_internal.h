@@ -11,6 +11,8 @@
 #include "singletop.h"
 #include "ttbar_dyn.h"
 
+#include <type_traits>
+
 namespace vgx {
 
 struct IterRecord {
@@ -62,67 +64,23 @@ __device__ __forceinline__ double grid_map(const double (&u)[D], const double* s
   return jac;
 }
 
-// The same map with the edge pairs of the odd dimensions read from global
-// memory (one 16-byte load, served by the L1: the grid is a few KB) instead
-// of LDS, for kernels whose LDS is their limit and whose vector-memory path
-// is otherwise idle.  The edges are the same, so is the result.
+// The grid map of caller points from scaled coordinates t_j = u_j N: i =
+// floor(t) clamped into [0, N-1] (points on or outside the cube's faces),
+// delta = t - i, x = e_i + delta w_i (w_i = e_{i+1} - e_i), J = N^D prod_j w_i
+// with the factor N^D given as nbD.  GLOBAL: the edge pairs come from global
+// memory (one 16-byte load each, served by the L1: the grid is a few KB),
+// else from LDS.
 typedef double double2_a8 __attribute__((ext_vector_type(2), aligned(8)));
-template <int D>
-__device__ __forceinline__ double grid_map_split(const double (&u)[D], const double* se,
-                                                 const double* __restrict__ ge, int nb, double (&x)[D],
-                                                 int (&idx)[D]) {
-  double jac = 1.0;
-  const double dnb = (double)nb;
-#pragma unroll
-  for (int j = 0; j < D; ++j) {
-    const double t = u[j] * dnb;
-    int i = (int)t;
-    i = i < nb - 1 ? i : nb - 1;
-    i = i > 0 ? i : 0;
-    const double delta = t - (double)i;
-    double lo, w;
-    if (j & 1) {
-      const double2_a8 e = *(const double2_a8*)(ge + j * (nb + 1) + i);
-      lo = e.x;
-      w = e.y - lo;
-    } else {
-      lo = se[j * (nb + 1) + i];
-      w = se[j * (nb + 1) + i + 1] - lo;
-    }
-    x[j] = fma(delta, w, lo);
-    jac *= dnb * w;
-    idx[j] = i;
-  }
-  return jac;
-}
-
-// The grid map from scaled coordinates t_j = u_j N (exactly representable
-// for the sources here): i = floor(t), delta = t - i, x = e_i + delta w_i
-// (w_i = e_{i+1} - e_i), J = N^D prod_j w_i with the factor N^D given as nbD.
-// INTERIOR: the source guarantees 0 < t < N (Philox uniforms), so i needs no
-// clamp and delta is fract(t); else i is clamped into [0, N-1] (caller
-// points on or outside the cube's faces) and delta = t - i.  GLOBAL: the
-// edge pairs come from global memory (one 16-byte load each, served by the
-// L1: the grid is a few KB), else from LDS.  Integrands without LDS tables
-// take GLOBAL: their LDS holds the histogram copies, whose atomics are the
-// LDS's load; with the edges too it was the limit (d = 4 Gaussian, 1e9
-// samples: 4.76 ms all in LDS, 4.00 ms with the odd dimensions in global
-// memory, 3.83 ms with all of them).
-template <int D, bool INTERIOR, bool GLOBAL>
+template <int D, bool GLOBAL>
 __device__ __forceinline__ double grid_map_t(const double (&t)[D], const double* se, const double* __restrict__ ge,
                                              int nb, double nbD, double (&x)[D], int (&idx)[D]) {
   double jw = 1.0;
 #pragma unroll
   for (int j = 0; j < D; ++j) {
     int i = (int)t[j];
-    double delta;
-    if constexpr (INTERIOR) {
-      delta = __builtin_amdgcn_fract(t[j]);
-    } else {
-      i = i < nb - 1 ? i : nb - 1;
-      i = i > 0 ? i : 0;
-      delta = t[j] - (double)i;
-    }
+    i = i < nb - 1 ? i : nb - 1;
+    i = i > 0 ? i : 0;
+    const double delta = t[j] - (double)i;
     double lo, w;
     if constexpr (GLOBAL) {
       // a 32-bit byte offset from the uniform base (a scalar-base load)
@@ -139,6 +97,52 @@ __device__ __forceinline__ double grid_map_t(const double (&t)[D], const double*
     idx[j] = i;
   }
   return jw * nbD;
+}
+
+// The grid map of Philox words k_j, u_j = (k_j + 1/2) 2^-32: one 64-bit
+// multiply-add k_j N + floor(N/2) has the bin in its upper word and the position
+// in it, f_j 2^-32 (for odd N less half a step), in its lower, both exact.
+// The bins' table holds (e_i, w_i 2^-32), for odd N e_i moved by that half step,
+// so that x = e_i + f_j w_i is one FMA and the width needs no subtraction;
+// for even N x is bit for bit that of the map above.  Per dimension
+// two instructions find the bin and the position (the conversion to FP64,
+// scaling, truncation and fraction were four) and one subtraction goes: with
+// the leaner exponential 111 -> 100 VALU instructions per sample for the d = 4
+// Gaussian, 3.35 -> 2.95 ms for 1e9 samples.  The table is read
+// from global memory, one 16-byte load per dimension served by the L1 (a few
+// KB): the LDS's load is the histogram's atomics and the integrand's tables.
+// J = nbDs prod_j w_j 2^-32, nbDs = (N 2^32)^D.
+__host__ __device__ inline double2 grid_bin(double lo, double hi, int nb) {
+  const double w = (hi - lo) * 0x1p-32;
+  return double2{(nb & 1) ? fma(0.5, w, lo) : lo, w};
+}
+template <int D>
+__device__ __forceinline__ double grid_map_words(const uint32_t (&k)[D], const double2* __restrict__ bins, int nb,
+                                                 double nbDs, double (&x)[D], int (&idx)[D]) {
+  double jw = nbDs;  // first, so that no partial product leaves the FP64 range before J does
+#pragma unroll
+  for (int j = 0; j < D; ++j) {
+    const uint64_t p = (uint64_t)k[j] * (uint32_t)nb + (uint32_t)(nb >> 1);
+    uint32_t i = (uint32_t)(p >> 32);
+    asm("" : "+v"(i));  // keeps the shift below apart from the 64-bit one
+    // a 32-bit byte offset from the uniform base (a scalar-base load)
+    const double2 e = *(const double2*)((const char*)(bins + j * nb) + (i << 4));
+    x[j] = fma((double)(uint32_t)p, e.y, e.x);
+    jw *= e.y;
+    idx[j] = (int)i;
+  }
+  return jw;
+}
+
+// The value of an integrand at a point the grid map made (inside the cube).
+template <class F, class = void>
+struct HasInside : std::false_type {};
+template <class F>
+struct HasInside<F, std::void_t<decltype(&F::eval_inside)>> : std::true_type {};
+template <class F, int D>
+__device__ __forceinline__ double eval_inside(const F& f, const double (&x)[D]) {
+  if constexpr (HasInside<F>::value) return f.eval_inside(x);
+  else return f.eval(x);
 }
 
 // Compensated sums of paired rows or halves of a wave, the lower one first.
@@ -273,8 +277,10 @@ __device__ inline void finalize_record(double s1, double s2, int64_t n, IterReco
 // registers; sums and the cumulative r are wave scans (three serial loops
 // of one thread over the bins took most of the 5.4 us that the kernel had for
 // 50 bins).
-__device__ inline void refine_dim(double* __restrict__ ej, const double* __restrict__ hj, int nb, double alpha) {
+__device__ inline void refine_dim(double* __restrict__ ej, double2* __restrict__ bj, const double* __restrict__ hj,
+                                  int nb, double alpha) {
   __shared__ double d[VGX_MAX_BINS], r[VGX_MAX_BINS], cum[VGX_MAX_BINS + 1], e[VGX_MAX_BINS + 1];
+  double* en = d;  // the new edges 1 .. nb - 1, once d has been read
   constexpr int CMAX = VGX_MAX_BINS / 64;
   const int lane = threadIdx.x & 63;
   const int C = (nb + 63) >> 6, i0 = lane * C;
@@ -336,11 +342,14 @@ __device__ inline void refine_dim(double* __restrict__ ej, const double* __restr
       frac = (target - cum[i]) / r[i];
       frac = frac < 0.0 ? 0.0 : (frac > 1.0 ? 1.0 : frac);
     }
-    ej[k] = e[i] + frac * (e[i + 1] - e[i]);
+    ej[k] = en[k] = e[i] + frac * (e[i + 1] - e[i]);
   }
+  __syncthreads();
+  for (int k = lane; k < nb; k += 64)
+    bj[k] = grid_bin(k == 0 ? e[0] : en[k], k == nb - 1 ? e[nb] : en[k + 1], nb);
 }
 
-// The context's pinned memory; the grid [dim][nb+1] follows.
+// The context's pinned memory; the grid (edges and bins) follows.
 struct PinnedHost {
   IterRecord rec[MAX_RECORDS];
   Combined comb;
@@ -365,7 +374,8 @@ struct vgx_vegas {
   int tt_dyn = 0;
   int max_wg = 0;
   int pstride = 0;
-  double* edges = nullptr;          // [dim][nb+1]
+  double* edges = nullptr;          // [dim][nb+1], then the bins
+  double2* bins = nullptr;          // [dim][nb] grid_bin of the edges, in the same allocation
   double* hist = nullptr;           // [dim][nb]
   double* partials = nullptr;       // [max_wg][pstride]
   float* tables = nullptr;          // the integrand's LDS tables, staged once (hadronic kinds)
@@ -382,6 +392,9 @@ struct vgx_vegas {
   int64_t pend_n = 0;               // its sample count
   double judge_var = -1.0;          // n var(E) of the latest plain iteration read back (< 0: none)
   bool have_hist = false;
+  // doubles of the edges (even, so that the bins are aligned) and of both
+  size_t edge_doubles() const { return ((size_t)dim * (nb + 1) + 1) & ~(size_t)1; }
+  size_t grid_doubles() const { return edge_doubles() + 2 * (size_t)dim * nb; }
   vgx::PinnedHost* host() const { return (vgx::PinnedHost*)pinned; }
   // kernel timing: event pairs recorded around the fused kernel, read back
   // (and summed) only when asked for, so timing does not synchronise
