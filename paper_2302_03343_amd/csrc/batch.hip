@@ -15,8 +15,8 @@
 //     pops tile indices from an atomic counter, so integrals with 1e4 and
 //     1e7 samples load-balance across the 256 CUs; the grid's bins are read
 //     from global memory (L1), so nothing is staged per tile;
-//   * the tile's histogram is kept in up to four LDS copies (lane l adds into
-//     copy l mod copies) and summed in copy order;
+//   * the tile's histogram has up to 16 columns per bin in LDS (lane l adds
+//     into column l mod columns), summed in a fixed order;
 //   * every tile writes its own partial row (S1, S2 compensated, histogram),
 //     so the reduction kernel sums each integral's rows in tile order: the
 //     result does not depend on which workgroup took which tile;
@@ -41,21 +41,22 @@
 namespace vgx {
 
 constexpr int BB_MAX = 256;  // launch bound of the persistent kernel
-// Copies of a tile's LDS histogram (1, 2 or 4 per batch, as many as fit in
-// kCopiesLds): lane l adds into copy l mod copies, so lanes of
-// one atomic instruction that fall into the same bin mostly hit different
-// addresses (LDS atomics on one address serialise); a copy is D nb + 1
-// doubles so that a bin's copies fall on different banks.  The copies are
-// summed in copy order when the tile's row is written.
-constexpr int kMaxHistCopies = 4;
-constexpr size_t kCopiesLds = 48 * 1024;
-__host__ __device__ inline int hist_stride(int dim, int nb) { return dim * nb + 1; }
-__host__ __device__ inline size_t batch_lds_bytes(int dim, int nb, int copies) {
-  return sizeof(double) * (size_t)copies * hist_stride(dim, nb);
+// A tile's histogram in LDS: [dim nb][columns] doubles, lane l adding into
+// column l mod columns, up to 16 columns per integral, as many as fit in
+// kColsLds (four workgroups per CU).  LDS executes an FP64 atomic 16 lanes at a time,
+// each group as often as its fullest bank pair has lanes: with random bins
+// 27.6 clocks per wave instruction, with 8 columns 18.0, with 16 10.3.
+constexpr size_t kColsLds = 40 * 1024;
+constexpr int kMaxColsLog2 = 4;
+inline int hist_shift(int dim, int nb) {
+  int s = 0;
+  while (s < kMaxColsLog2 && (sizeof(double) * dim * nb) << (s + 1) <= kColsLds) ++s;
+  return s;
 }
 
 struct BatchItem {
   int kind, prec, dim, nb;
+  int shift;             // log2 of the LDS histogram's columns
   uint32_t sid, k0, k1;
   int pstride;           // 4 + dim * nb
   int64_t n;             // samples per iteration
@@ -106,7 +107,7 @@ __device__ __forceinline__ void run_tile(const BatchItem& it, const F& f, double
     p1 += w;
     p2 += w2;
 #pragma unroll
-    for (int j = 0; j < D; ++j) atomicAdd(&sh[j * it.nb + idx[j]], w2);
+    for (int j = 0; j < D; ++j) atomicAdd(&sh[(j * it.nb + idx[j]) << it.shift], w2);
   }
   c1.add(p1);
   c2.add(p2);
@@ -139,7 +140,7 @@ __global__ void k_batch_begin(BatchState* st) {
 }
 
 __global__ __launch_bounds__(BB_MAX) void k_batch(const BatchItem* __restrict__ items, int count, int64_t total_tiles,
-                                                 int tile, int copies, BatchState* __restrict__ st,
+                                                 int tile, BatchState* __restrict__ st,
                                                  double* __restrict__ partials) {
   extern __shared__ double lds[];
   __shared__ int64_t s_tile;
@@ -163,14 +164,14 @@ __global__ __launch_bounds__(BB_MAX) void k_batch(const BatchItem* __restrict__ 
     if (t >= total_tiles) break;  // uniform: every wave leaves
     const int k = s_item;
     const BatchItem& it = items[k];
-    const int hs = hist_stride(it.dim, it.nb);
-    for (int q = threadIdx.x; q < copies * hs; q += blockDim.x) sh[q] = 0.0;
+    const int cols = 1 << it.shift;
+    for (int q = threadIdx.x; q < (it.dim * it.nb) << it.shift; q += blockDim.x) sh[q] = 0.0;
     __syncthreads();
     const int64_t lt = t - it.tile0;
     const int64_t s0 = lt * tile;
     const int64_t s1 = (s0 + tile < it.n) ? s0 + tile : it.n;
     Comp c1, c2;
-    double* shl = sh + (threadIdx.x & (copies - 1)) * hs;  // this lane's histogram copy
+    double* shl = sh + (threadIdx.x & (cols - 1));  // this lane's column
     switch (it.dim) {
       case 1: run_tile_d<1>(it, shl, s0, s1, iter, c1, c2); break;
       case 2: run_tile_d<2>(it, shl, s0, s1, iter, c1, c2); break;
@@ -196,8 +197,9 @@ __global__ __launch_bounds__(BB_MAX) void k_batch(const BatchItem* __restrict__ 
       row[threadIdx.x] = s;
     }
     for (int q = threadIdx.x; q < it.dim * it.nb; q += blockDim.x) {
-      double h = sh[q];
-      for (int c = 1; c < copies; ++c) h += sh[c * hs + q];
+      // from column q mod cols round: neighbouring q on different banks
+      double h = 0.0;
+      for (int c = 0; c < cols; ++c) h += sh[(q << it.shift) + ((c + q) & (cols - 1))];
       row[4 + q] = h;
     }
     __syncthreads();  // LDS histogram and s_tile are reused by the next tile
@@ -280,7 +282,6 @@ struct vgx_batch {
   double* partials = nullptr;
   size_t part_cap = 0;               // doubles
   int tile = 0, block = 0, grid = 0;
-  int copies = 1;                    // LDS histogram copies per workgroup
   int64_t total_tiles = 0;
   size_t lds = 0;
   int max_cols = 0;
@@ -322,7 +323,7 @@ vgx_status upload_items(vgx_batch* b, hipStream_t st) {
 vgx_status enqueue_iteration(vgx_batch* b, hipStream_t st, bool refine) {
   hipLaunchKernelGGL(k_batch_begin, dim3(1), dim3(64), 0, st, b->d_state);
   hipLaunchKernelGGL(k_batch, dim3(b->grid), dim3(b->block), b->lds, st, b->d_items, b->count, b->total_tiles,
-                     b->tile, b->copies, b->d_state, b->partials);
+                     b->tile, b->d_state, b->partials);
   if (refine) {
     hipLaunchKernelGGL(k_batch_reduce, dim3((b->max_cols + BR_COLS - 1) / BR_COLS, b->count),
                        dim3(BR_GROUPS * BR_COLS), 0, st, b->d_items,
@@ -411,7 +412,6 @@ extern "C" vgx_status batch_create(vgx_vegas* const* ctxs, int32_t count, const 
   b->ctx.assign(ctxs, ctxs + count);
   b->n.assign(n_samples, n_samples + count);
   b->items.resize(count);
-  size_t max_lds[3] = {0, 0, 0};  // workgroup LDS with 1, 2, 4 histogram copies
   for (int k = 0; k < count; ++k) {
     const vgx_vegas* c = ctxs[k];
     BatchItem it{};
@@ -419,6 +419,7 @@ extern "C" vgx_status batch_create(vgx_vegas* const* ctxs, int32_t count, const 
     it.prec = c->prec;
     it.dim = c->dim;
     it.nb = c->nb;
+    it.shift = hist_shift(c->dim, c->nb);
     it.sid = c->stream_id;
     it.k0 = (uint32_t)c->seed;
     it.k1 = (uint32_t)(c->seed >> 32);
@@ -432,11 +433,9 @@ extern "C" vgx_status batch_create(vgx_vegas* const* ctxs, int32_t count, const 
     it.comb = c->comb;
     it.prm = c->prm;
     b->items[k] = it;
-    for (int q = 0; q < 3; ++q) max_lds[q] = std::max(max_lds[q], batch_lds_bytes(c->dim, c->nb, 1 << q));
+    b->lds = std::max(b->lds, (sizeof(double) * c->dim * c->nb) << it.shift);
     b->max_cols = it.pstride > b->max_cols ? it.pstride : b->max_cols;
   }
-  b->copies = max_lds[2] <= kCopiesLds ? 4 : (max_lds[1] <= kCopiesLds ? 2 : 1);
-  b->lds = max_lds[b->copies == 4 ? 2 : b->copies - 1];
   vgx_status s = VGX_OK;
   do {
     b->part_cap = partial_doubles(b, tile > 0 ? tile : 2048);
