@@ -17,6 +17,7 @@
 #include "pdf_lds.h"
 
 #include <float.h>
+#include <algorithm>
 #include <math.h>
 #include <type_traits>
 #include <stdlib.h>
@@ -359,98 +360,209 @@ __global__ __launch_bounds__(256) void k_pdf_interp(PdfKernelArgs g, int64_t n, 
   }
 }
 
+// Largest of v over the wave's lanes (in lane 63).
+__device__ __forceinline__ int wave_max_last(int v) {
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x111, 0xF, 0xF, false));  // row_shr:1, 2, 4, 8
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x112, 0xF, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x114, 0xF, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x118, 0xF, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x142, 0xA, 0xF, false));  // row_bcast15
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xC, 0xF, false));  // row_bcast31
+  return v;
+}
+
 // Several members of a PDF set at the same points (the thesis's multi-member
-// evaluation for FastKernel-type convolutions): blockIdx.y is the member, so
-// a wave takes 64 consecutive points of one member and its stores are
-// contiguous; a set of N_rep members at a few thousand points still fills the
-// chip.  One (point, member) per lane, each lane reading its stencil rows as
-// 16-byte loads, in the weights and summation order of k_pdf_interp.  This
-// workload is small (a few thousand points per member, a couple of waves'
-// worth of work per member for each CU), and there one query per lane,
-// with its higher occupancy, measured 1.25x faster than the cooperative
-// gathers of k_pdf_interp.  Outside the grid: NaN (counted once
-// per point, by member 0), whatever the context's extrapolation mode.
-template <typename OutT, typename ValT, int NF>
-__global__ __launch_bounds__(256) void k_pdf_members(PdfKernelArgs g, int64_t n, int64_t member_stride,
+// evaluation for FastKernel-type convolutions): a lane takes one point of
+// members blockIdx.y, blockIdx.y + gridDim.y, ..., so a wave's stores are
+// contiguous and the cells and weights, which do not depend on the member, are
+// found once for all of them; a set of N_rep members at a few thousand points
+// still fills the chip.  The values are the weights and the summation order of
+// k_pdf_interp.
+//
+// Read from memory, a lane's 16 nodes are 88 (FP64, 11 flavours) 16-byte loads,
+// and the L1 returns 64 bytes per clock whatever the lanes share: 98 loads
+// per wave took two thirds of the kernel's time.  The points of a table are
+// neighbours, so the workgroup's stencils lie in a box of few nodes: where
+// the box (from the smallest to the largest node index on each axis) fits in
+// box_bytes of LDS, it is copied there, a node padded to a multiple of 16
+// bytes, and read back at 128 bytes per clock, lanes of one cell in one
+// access (100 members at 2415 points, FP64: 17.6 -> 12.7 us; 400 at 5000: 99.7
+// -> 45).  Points far apart (a box too large) read memory (400 x 5000 random
+// points: 727 -> 482 us, by the weights found once).  Outside the grid: NaN
+// (counted once per point), whatever the context's extrapolation mode.
+template <typename ValT, int NF, int W>
+__device__ __forceinline__ void members_sums(double (&acc)[NF > 0 ? NF : VGX_MAX_FLAV], const ValT* V, int64_t row,
+                                             int node_stride, int nf, const double (&cx)[4], const double (&cq)[4]) {
+  constexpr int NFM = NF > 0 ? NF : VGX_MAX_FLAV;
+#pragma unroll
+  for (int r = 0; r < W; ++r)
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+      const double w = cq[r] * cx[k];
+      const ValT* node = V + r * row + k * node_stride;
+#pragma unroll
+      for (int f = 0; f < NFM; ++f)
+        if (f < nf) acc[f] = fma(w, (double)node[f], acc[f]);
+    }
+}
+
+// The same from the LDS box: 16-byte reads.
+template <typename ValT, int NF, int W>
+__device__ __forceinline__ void members_sums_lds(double (&acc)[NF > 0 ? NF : VGX_MAX_FLAV], const ValT* V, int row,
+                                                 int node_stride, int nf, const double (&cx)[4],
+                                                 const double (&cq)[4]) {
+  constexpr int NFM = NF > 0 ? NF : VGX_MAX_FLAV;
+  constexpr int VPL = 16 / sizeof(ValT);
+  typedef ValT vec __attribute__((ext_vector_type(VPL)));
+#pragma unroll
+  for (int r = 0; r < W; ++r)
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+      const double w = cq[r] * cx[k];
+      const vec* node = (const vec*)(V + r * row + k * node_stride);
+#pragma unroll
+      for (int u = 0; u < (NFM + VPL - 1) / VPL; ++u)
+        if (u * VPL < nf) {
+          const vec v = node[u];
+#pragma unroll
+          for (int e = 0; e < VPL; ++e)
+            if (u * VPL + e < NFM && u * VPL + e < nf) acc[u * VPL + e] = fma(w, (double)v[e], acc[u * VPL + e]);
+        }
+    }
+}
+
+// values per node of the LDS box
+template <typename ValT>
+__host__ __device__ constexpr int box_stride(int nf) {
+  return (nf + (int)(16 / sizeof(ValT)) - 1) & ~((int)(16 / sizeof(ValT)) - 1);
+}
+
+template <typename OutT, typename ValT, int NF, bool BOX>
+__global__ __launch_bounds__(256, BOX && NF > 0 ? 4 : 1) void k_pdf_members(PdfKernelArgs g, int64_t n, int n_members, int64_t member_stride,
+                                                     int box_bytes,
                                                      const double* __restrict__ qx, const double* __restrict__ qq2,
                                                      const double* __restrict__ kx, const double* __restrict__ klx,
                                                      const double* __restrict__ kq2, const double* __restrict__ klq2,
                                                      const ValT* __restrict__ vals, OutT* __restrict__ out,
                                                      unsigned long long* __restrict__ oor) {
   constexpr int NFM = NF > 0 ? NF : VGX_MAX_FLAV;
-  extern __shared__ double lds[];
+  extern __shared__ __align__(16) double lds[];
   double* sx = lds;
   double* slx = sx + g.n_x;
   const int nqt = g.q_off[g.n_sub];
   double* sq2 = slx + g.n_x;
   double* slq2 = sq2 + nqt;
+  ValT* box = (ValT*)(slq2 + nqt);  // after an even number of doubles
+  __shared__ int ext[4][4];         // per wave: -(x lo), x hi, -(row lo), row hi
   for (int k = threadIdx.x; k < g.n_x; k += blockDim.x) { sx[k] = kx[k]; slx[k] = klx[k]; }
   for (int k = threadIdx.x; k < nqt; k += blockDim.x) { sq2[k] = kq2[k]; slq2[k] = klq2[k]; }
   __syncthreads();
   const int nf = NF > 0 ? NF : g.n_flav;
-  const int m = blockIdx.y;
-  const ValT* Vm = vals + (int64_t)m * member_stride;
-  OutT* om = out + (int64_t)m * nf * n;
+  const int NS = box_stride<ValT>(nf);
+  const int ms = gridDim.y;  // the lane's members blockIdx.y + k ms
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += stride) {
-    const double x = qx[q];
-    const double q2 = qq2[q];
-    int s = -1;
-    for (int k = 0; k < g.n_sub; ++k) {
-      const bool last = (k == g.n_sub - 1);
-      if (q2 >= g.q2_lo[k] && (q2 < g.q2_hi[k] || (last && q2 <= g.q2_hi[k]))) s = k;
-    }
-    if (s < 0 || !(x >= sx[0] && x <= sx[g.n_x - 1])) {
-      for (int f = 0; f < nf; ++f) om[(int64_t)f * n + q] = (OutT)NAN;
-      if (m == 0) atomicAdd(oor, 1ull);
-      continue;
-    }
-    const int nq = g.nq[s];
-    const double* lq = slq2 + g.q_off[s];
-    const int i = find_cell(sx, g.n_x, x);
-    const int j = find_cell(sq2 + g.q_off[s], nq, q2);
-    const double a = log(x), b = log(q2);
-    const ValT* V = Vm + (int64_t)g.q_off[s] * g.n_x * nf;
-    double acc[NFM];
-#pragma unroll
-    for (int f = 0; f < NFM; ++f) acc[f] = 0.0;
-    if (i >= 1 && i <= g.n_x - 3 && j >= 1 && j <= nq - 3) {
-      const double ha = slx[i + 1] - slx[i];
-      const double hb = lq[j + 1] - lq[j];
-      double cx[4], cq[4];
-      hermite_weights((a - slx[i]) / ha, ha / (slx[i] - slx[i - 1]), ha / (slx[i + 2] - slx[i + 1]), cx);
-      hermite_weights((b - lq[j]) / hb, hb / (lq[j] - lq[j - 1]), hb / (lq[j + 2] - lq[j + 1]), cq);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const ValT* row = V + ((int64_t)(j - 1 + r) * g.n_x + (i - 1)) * nf;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const double w = cq[r] * cx[k];
-          const ValT* node = row + k * nf;
-#pragma unroll
-          for (int f = 0; f < NFM; ++f)
-            if (f < nf) acc[f] = fma(w, (double)node[f], acc[f]);
-        }
+  for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < n; base += stride) {  // uniform per workgroup
+    const int64_t q = base + threadIdx.x;
+    bool in = false, full = false;
+    int i0 = 0, r0 = 0;  // the stencil's first node: x index, row
+    double cx[4], cq[4];
+    if (q < n) {
+      const double x = qx[q];
+      const double q2 = qq2[q];
+      int s = -1;
+      for (int k = 0; k < g.n_sub; ++k) {
+        const bool last = (k == g.n_sub - 1);
+        if (q2 >= g.q2_lo[k] && (q2 < g.q2_hi[k] || (last && q2 <= g.q2_hi[k]))) s = k;
       }
-    } else {
-      const double ta = (a - slx[i]) / (slx[i + 1] - slx[i]);
-      const double tb = (b - lq[j]) / (lq[j + 1] - lq[j]);
-      const double w[4] = {(1.0 - ta) * (1.0 - tb), ta * (1.0 - tb), (1.0 - ta) * tb, ta * tb};
-#pragma unroll
-      for (int r = 0; r < 2; ++r) {
-        const ValT* row = V + ((int64_t)(j + r) * g.n_x + i) * nf;
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          const ValT* node = row + k * nf;
-#pragma unroll
-          for (int f = 0; f < NFM; ++f)
-            if (f < nf) acc[f] = fma(w[2 * r + k], (double)node[f], acc[f]);
+      in = s >= 0 && x >= sx[0] && x <= sx[g.n_x - 1];
+      if (!in) {
+        for (int m = blockIdx.y; m < n_members; m += ms)
+          for (int f = 0; f < nf; ++f) out[((int64_t)m * nf + f) * n + q] = (OutT)NAN;
+        if (blockIdx.y == 0) atomicAdd(oor, 1ull);
+      } else {
+        const int nq = g.nq[s];
+        const double* lq = slq2 + g.q_off[s];
+        const int i = find_cell(sx, g.n_x, x);
+        const int j = find_cell(sq2 + g.q_off[s], nq, q2);
+        const double a = log(x), b = log(q2);
+        full = i >= 1 && i <= g.n_x - 3 && j >= 1 && j <= nq - 3;
+        if (full) {
+          const double ha = slx[i + 1] - slx[i];
+          const double hb = lq[j + 1] - lq[j];
+          hermite_weights((a - slx[i]) / ha, ha / (slx[i] - slx[i - 1]), ha / (slx[i + 2] - slx[i + 1]), cx);
+          hermite_weights((b - lq[j]) / hb, hb / (lq[j] - lq[j - 1]), hb / (lq[j + 2] - lq[j + 1]), cq);
+        } else {
+          const double ta = (a - slx[i]) / (slx[i + 1] - slx[i]);
+          const double tb = (b - lq[j]) / (lq[j + 1] - lq[j]);
+          cx[0] = 1.0 - ta; cx[1] = ta;
+          cq[0] = 1.0 - tb; cq[1] = tb;
         }
+        i0 = i - (full ? 1 : 0);
+        r0 = g.q_off[s] + j - (full ? 1 : 0);
       }
     }
+    bool boxed = false;
+    int xlo = 0, rlo = 0, bx = 0, br = 0;
+    if constexpr (BOX) {
+      const int w1 = full ? 3 : 1, none = -(1 << 30);
+      const int e0 = wave_max_last(in ? -i0 : none), e1 = wave_max_last(in ? i0 + w1 : none);
+      const int e2 = wave_max_last(in ? -r0 : none), e3 = wave_max_last(in ? r0 + w1 : none);
+      __syncthreads();  // ext has been read
+      if ((threadIdx.x & 63) == 63) {
+        const int wv = threadIdx.x >> 6;
+        ext[wv][0] = e0; ext[wv][1] = e1; ext[wv][2] = e2; ext[wv][3] = e3;
+      }
+      __syncthreads();
+      int lim[4];
 #pragma unroll
-    for (int f = 0; f < NFM; ++f)
-      if (f < nf) om[(int64_t)f * n + q] = (OutT)acc[f];
+      for (int c = 0; c < 4; ++c) lim[c] = max(max(ext[0][c], ext[1][c]), max(ext[2][c], ext[3][c]));
+      xlo = -lim[0];
+      rlo = -lim[2];
+      bx = lim[1] - xlo + 1;  // negative: no point inside
+      br = lim[3] - rlo + 1;
+      boxed = bx > 0 && (int64_t)bx * br * NS * (int)sizeof(ValT) <= box_bytes;
+    }
+    const int64_t row = (int64_t)g.n_x * nf;
+    int m = blockIdx.y;
+    do {
+      const ValT* Vm = vals + m * member_stride;
+      double acc[NFM];
+#pragma unroll
+      for (int f = 0; f < NFM; ++f) acc[f] = 0.0;
+      if (BOX && boxed) {  // uniform per workgroup
+        __syncthreads();  // the previous box has been read
+        const ValT* src = Vm + rlo * row + (int64_t)xlo * nf;
+        const int len = bx * nf;
+        for (int r = threadIdx.x >> 6; r < br; r += 4)  // a wave per row, eight loads in flight
+          for (int e0 = threadIdx.x & 63; e0 < len; e0 += 512) {
+            ValT v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = e0 + 64 * u < len ? src[r * row + e0 + 64 * u] : (ValT)0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+              const int e = e0 + 64 * u, node = e / nf;
+              if (e < len) box[(r * bx + node) * NS + (e - node * nf)] = v[u];
+            }
+          }
+        __syncthreads();
+        if (in) {
+          const ValT* V = box + ((r0 - rlo) * bx + (i0 - xlo)) * NS;
+          if (full) members_sums_lds<ValT, NF, 4>(acc, V, bx * NS, NS, nf, cx, cq);
+          else members_sums_lds<ValT, NF, 2>(acc, V, bx * NS, NS, nf, cx, cq);
+        }
+      } else if (in) {
+        const ValT* V = Vm + r0 * row + (int64_t)i0 * nf;
+        if (full) members_sums<ValT, NF, 4>(acc, V, row, nf, nf, cx, cq);
+        else members_sums<ValT, NF, 2>(acc, V, row, nf, nf, cx, cq);
+      }
+      if (in) {
+        OutT* om = out + (int64_t)m * nf * n;
+#pragma unroll
+        for (int f = 0; f < NFM; ++f)
+          if (f < nf) om[(int64_t)f * n + q] = (OutT)acc[f];
+      }
+      m += ms;
+    } while (BOX && m < n_members);
   }
 }
 
@@ -828,6 +940,13 @@ extern "C" vgx_status pdf_interp(const vgx_pdf* p, int64_t n, const double* x_de
   return VGX_OK;
 }
 
+// Values (members x points) from which the LDS box is used.  Below, the box's
+// setup and the fewer workgroups cost as much as the loads: 400 members at 100
+// points 10.5 us from memory, 12.2 with the box; FP32, whose loads are half as
+// many, 100 at 2415 13.2 and 13.8.
+constexpr int64_t kMembersBox64 = 150000, kMembersBox32 = 450000;
+constexpr size_t kMembersBox = 32 * 1024;
+
 extern "C" vgx_status pdf_interp_members(const vgx_pdf* p, int64_t n, const double* x_dev, const double* q2_dev,
                                          int32_t out_dtype, void* out_dev, void* stream) {
   VGX_CHECK(p, "pdf_interp_members: null context");
@@ -846,28 +965,44 @@ extern "C" vgx_status pdf_interp_members(const vgx_pdf* p, int64_t n, const doub
   g.q_off[p->n_sub] = p->q_off[p->n_sub];
   const int64_t stride = (int64_t)p->q_off[p->n_sub] * p->n_x * p->n_flav;
   const int block = 256;
-  // blocks per member: enough to cover the points, the chip filled across members
+  // Small calls: a member per lane, from memory.  Large ones: the LDS box, two
+  // or more members per lane, at most eight blocks per CU.
+  const bool boxed = (int64_t)p->n_members * n >= (out_dtype == VGX_F64 ? kMembersBox64 : kMembersBox32);
   const int64_t want = (n + block - 1) / block;
-  int64_t cap = (int64_t)device_cus() * 8 / p->n_members;
-  cap = cap < 1 ? 1 : cap;
-  const dim3 grid((unsigned)(want < cap ? want : cap), (unsigned)p->n_members);
-  const size_t lds = sizeof(double) * (2 * (size_t)p->n_x + 2 * (size_t)p->q_off[p->n_sub]);
+  const int64_t room = (int64_t)device_cus() * 8;
+  int64_t gx, gy = p->n_members;
+  if (boxed) {
+    gx = want < room ? want : room;
+    gy = std::min((gy + 1) / 2, (room + gx - 1) / gx);
+    const int64_t each = (p->n_members + gy - 1) / gy;
+    gy = (p->n_members + each - 1) / each;  // even shares
+  } else {
+    const int64_t cap = std::max<int64_t>(room / gy, 1);  // the chip filled across members
+    gx = want < cap ? want : cap;
+  }
+  const dim3 grid((unsigned)gx, (unsigned)gy);
+  const size_t knots = sizeof(double) * (2 * (size_t)p->n_x + 2 * (size_t)p->q_off[p->n_sub]);
+  const size_t box =
+      boxed ? std::min(kMembersBox, (kMaxLds - 1024 - std::min(knots, kMaxLds - 1024)) & ~(size_t)15) : 0;
+  const size_t lds = knots + box;
   hipStream_t st = (hipStream_t)stream;
+  auto launch = [&](auto k, const auto* vals, auto* out) {
+    hipLaunchKernelGGL(k, grid, dim3(block), lds, st, g, n, p->n_members, stride, (int)box, x_dev, q2_dev, p->x, p->lx,
+                       p->q2, p->lq2, vals, out, p->oor);
+  };
   const bool f11 = p->n_flav == 11;
   if (out_dtype == VGX_F64) {
-    if (f11)
-      hipLaunchKernelGGL((k_pdf_members<double, double, 11>), grid, dim3(block), lds, st, g, n, stride, x_dev, q2_dev,
-                         p->x, p->lx, p->q2, p->lq2, p->v64, (double*)out_dev, p->oor);
-    else
-      hipLaunchKernelGGL((k_pdf_members<double, double, 0>), grid, dim3(block), lds, st, g, n, stride, x_dev, q2_dev,
-                         p->x, p->lx, p->q2, p->lq2, p->v64, (double*)out_dev, p->oor);
+    double* o = (double*)out_dev;
+    if (boxed) f11 ? launch(k_pdf_members<double, double, 11, true>, p->v64, o)
+                   : launch(k_pdf_members<double, double, 0, true>, p->v64, o);
+    else f11 ? launch(k_pdf_members<double, double, 11, false>, p->v64, o)
+             : launch(k_pdf_members<double, double, 0, false>, p->v64, o);
   } else {
-    if (f11)
-      hipLaunchKernelGGL((k_pdf_members<float, float, 11>), grid, dim3(block), lds, st, g, n, stride, x_dev, q2_dev,
-                         p->x, p->lx, p->q2, p->lq2, p->v32, (float*)out_dev, p->oor);
-    else
-      hipLaunchKernelGGL((k_pdf_members<float, float, 0>), grid, dim3(block), lds, st, g, n, stride, x_dev, q2_dev,
-                         p->x, p->lx, p->q2, p->lq2, p->v32, (float*)out_dev, p->oor);
+    float* o = (float*)out_dev;
+    if (boxed) f11 ? launch(k_pdf_members<float, float, 11, true>, p->v32, o)
+                   : launch(k_pdf_members<float, float, 0, true>, p->v32, o);
+    else f11 ? launch(k_pdf_members<float, float, 11, false>, p->v32, o)
+             : launch(k_pdf_members<float, float, 0, false>, p->v32, o);
   }
   VGX_HIP(hipGetLastError());
   return VGX_OK;
