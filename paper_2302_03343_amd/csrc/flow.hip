@@ -484,7 +484,7 @@ __global__ __launch_bounds__(FBLOCK) void k_flow_wgrad(const FlowDesc* __restric
 // The workgroup's WV waves (8 where the stages fit the LDS, two per SIMD,
 // else 4) take WV 32-sample tiles at a time (a group).  Each wave runs the
 // backward of its tile as k_flow_bwd does; the operands
-// of the weight-gradient products (deltas and activations, feature-major)
+// of the weight-gradient products (deltas and activations)
 // go to an LDS stage instead of global memory, one product at a time:
 // [dlogit | h2], then [dpre2 | h1], then [dpre1 | zA].  After each stage the
 // waves contract the group's tiles (K = 32 WV samples) into the
@@ -506,19 +506,28 @@ constexpr int FUSE_DMAX = 8;  // |B| <= 4 holds exactly for d <= 8
 
 // rows of a tile's stage: the largest of (32 |B| + 64), 128 and 96
 __host__ __device__ constexpr int fuse_stage_rows(int nb) { return 32 * nb + 64 > 128 ? 32 * nb + 64 : 128; }
-// row stride of a stage in elements: 32 samples, + 16 bytes of padding for
-// BF16 stages (the FP32 validation stages go without, to fit the LDS)
+// FP32 (validation) stages are feature-major, 32 samples per row.  BF16
+// stages are sample-major: a sample's features in a row of 256 (up to 128
+// features) or 512 bytes, four features (8 bytes) per chunk, chunk c at
+// position c ^ stage_swizzle(sample) of its 32.
+__host__ __device__ constexpr int fuse_row_bytes(int nb) { return fuse_stage_rows(nb) > 128 ? 512 : 256; }
 template <class OP>
-__host__ __device__ constexpr int fuse_rs() { return sizeof(typename OP::S) == 2 ? 40 : 32; }
+__host__ __device__ constexpr int fuse_stage_bytes(int nb) {
+  return sizeof(typename OP::S) == 2 ? 32 * fuse_row_bytes(nb) : fuse_stage_rows(nb) * 32 * 4;
+}
+// With it the writes (32 samples, one chunk) and the transposing reads (four
+// consecutive samples, eight chunks) both touch every LDS bank once.
+__device__ __forceinline__ int stage_swizzle(int sample) { return ((sample & 3) << 3) | (sample >> 2); }
 
 // LDS of the fused kernel with bs threads: packs and biases | per-lane
 // columns [2 d + 2][bs] (z, its gradient, a zero column, a sink column) |
-// stage [bs / 64][rows][rs]
+// stage [bs / 64]
 __host__ __device__ inline size_t fuse_z_offset(int fw_len, int bw_len, int bias_len, int es) {
   return bwd_z_offset(fw_len, bw_len, bias_len, es);
 }
 __host__ __device__ inline size_t fuse_stage_offset(int fw_len, int bw_len, int bias_len, int es, int d, int bs) {
-  return fuse_z_offset(fw_len, bw_len, bias_len, es) + sizeof(float) * (2 * (size_t)d + 2) * bs;
+  // (a multiple of 256: the chunk positions are XORed into byte addresses)
+  return (fuse_z_offset(fw_len, bw_len, bias_len, es) + sizeof(float) * (2 * (size_t)d + 2) * bs + 255) & ~(size_t)255;
 }
 
 // the two hidden layers of the network for the wave's 32 samples as operand
@@ -551,36 +560,108 @@ __device__ __forceinline__ void mlp_hidden_fb(const float (&za)[FAB], const Laye
   }
 }
 
-// fragment kk of a 32-row block into a stage, feature-major (row = feature,
-// column = sample): element e holds row row0 + drow(8 (kk & 1) + e, h)
-template <class OP>
-__device__ __forceinline__ void stage_put(typename OP::S* st, int row0, const typename OP::frag& f, int half, int s,
-                                          int h) {
-  constexpr int RS = fuse_rs<OP>();
+// A wave's view of the stages in LDS: writes into its own stage, operand
+// reads from all of them.  The products contract over the samples, so their
+// operands hold eight samples of one feature per lane, where the activations
+// and deltas hold eight features of one sample.  BF16: the lane writes its
+// features as they are (two 8-byte writes per fragment) and ds_read_tr16_b64
+// transposes on the way back: in each 16 lanes, lane t receives from lanes 4 e
+// + t / 4 (e = 0 .. 3) the element t mod 4 of their 8 bytes, so lane u points at
+// sample u / 4, features 4 (u mod 4) .. + 3, and receives four samples of feature
+// t.  (Feature-major stages took eight 2-byte writes per fragment, 176 instead
+// of 44 LDS writes per tile and wave: 31.1 us per launch at 1e5 samples for |B| =
+// 2 and 24.2 for 1, now 28.6 and 22.2.)
+template <class OP, int NB>
+struct Stage;
+
+template <int NB>
+struct Stage<OpBF16, NB> {
+  using frag = bf16x8;
+  static constexpr int RB = fuse_row_bytes(NB), SB = fuse_stage_bytes<OpBF16>(NB);
+  unsigned char* lds;
+  unsigned w0, z0, r0;  // byte offsets: the lane's writes, its own row, its reads of stage 0
+  __device__ __forceinline__ Stage(unsigned char* lds_, unsigned off, int wave) : lds(lds_) {
+    const int lane = threadIdx.x & 63, s = lane & 31, h = lane >> 5, t = lane & 15, gi = (lane >> 4) & 1;
+    z0 = off + wave * SB + s * RB;
+    w0 = z0 + ((stage_swizzle(s) ^ h) << 3);
+    r0 = off + (8 * h + (t >> 2)) * RB + ((((t >> 2) << 3) | ((4 * gi + (t & 3)) ^ (2 * h))) << 3);
+  }
+  __device__ __forceinline__ void put8(unsigned base, int c, unsigned lo, unsigned hi) const {
+    typedef unsigned u32x2v __attribute__((ext_vector_type(2)));
+    *(u32x2v*)(lds + (base ^ ((c & 31) << 3)) + (c >> 5) * 256) = u32x2v{lo, hi};
+  }
+  // fragment half (0 or 1) of the 32-row block at row0: element e holds row
+  // row0 + drow(8 half + e, h)
+  __device__ __forceinline__ void put(int row0, const frag& f, int half) const {
+    const u32x4v v = __builtin_bit_cast(u32x4v, f);
+    put8(w0, row0 / 4 + 4 * half, v[0], v[1]);
+    put8(w0, row0 / 4 + 4 * half + 2, v[2], v[3]);
+  }
+  // the network's input za as rows 64 .. 96 (zero beyond |A|)
+  __device__ __forceinline__ void put_input(const float (&za)[FAB]) const {
+    const int lane = threadIdx.x & 63, s = lane & 31, h = lane >> 5;
+    frag f;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) st[(row0 + drow(8 * half + e, h)) * RS + s] = FragOps<OP>::bits(f, e);
-}
+    for (int e = 0; e < 8; ++e) OpBF16::set(f, e, h == 0 ? za[e] : 0.0f);
+    const u32x4v v = __builtin_bit_cast(u32x4v, f);
+    const unsigned b = z0 + ((stage_swizzle(s) ^ (4 * h)) << 3);  // h = 0: rows 64 .. 80, h = 1: 80 .. 96
+    put8(b, 16, v[0], v[1]);
+    put8(b, 17, v[2], v[3]);
+    put8(b, 18, 0u, 0u);
+    put8(b, 19, 0u, 0u);
+  }
+  // operand of stage q: lane (i, h) holds row row0 + i, samples 16 kk + 8 h + e
+  __device__ __forceinline__ frag get(int q, int row0, int kk) const {
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    s16x4 v[2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const unsigned a = r0 ^ (((row0 / 32) & 3) << 6) ^ ((4 * kk + p) << 3);
+      v[p] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+          (lds_s16x4*)(lds + a + (row0 / 128) * 256 + q * SB + (16 * kk + 4 * p) * RB));
+    }
+    const s16x8 r = __builtin_shufflevector(v[0], v[1], 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(frag, r);
+  }
+};
 
-template <class OP>
-__device__ __forceinline__ typename OP::frag stage_get(const typename OP::S* st, int row, int kk, int h) {
-  constexpr int RS = fuse_rs<OP>();
-  return *(const typename OP::frag*)(st + row * RS + 16 * kk + 8 * h);
-}
+template <int NB>
+struct Stage<OpF32, NB> {
+  using frag = f32x8;
+  static constexpr int SE = fuse_stage_bytes<OpF32>(NB) / 4;
+  float* st;   // stage 0
+  float* own;
+  __device__ __forceinline__ Stage(unsigned char* lds, unsigned off, int wave)
+      : st((float*)(lds + off)), own((float*)(lds + off) + wave * SE) {}
+  __device__ __forceinline__ void put(int row0, const frag& f, int half) const {
+    const int lane = threadIdx.x & 63, s = lane & 31, h = lane >> 5;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) own[(row0 + drow(8 * half + e, h)) * 32 + s] = f[e];
+  }
+  __device__ __forceinline__ void put_input(const float (&za)[FAB]) const {
+    const int lane = threadIdx.x & 63, s = lane & 31, h = lane >> 5;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) own[(64 + 16 * h + e) * 32 + s] = (e < FAB && h == 0) ? za[e & (FAB - 1)] : 0.0f;
+  }
+  __device__ __forceinline__ frag get(int q, int row0, int kk) const {
+    const int lane = threadIdx.x & 63, i = lane & 31, h = lane >> 5;
+    return *(const frag*)(st + q * SE + (row0 + i) * 32 + 16 * kk + 8 * h);
+  }
+};
 
-// contract the group's NST stages: A rows arow0 + 32 m, B rows brow0 + 32 n
-template <class OP, int NST, int SR>
-__device__ __forceinline__ void fuse_contract(const typename OP::S* stage, int arow0, int brow0, int m, int n,
-                                              f32x16& acc, float& bsum) {
-  constexpr int RS = fuse_rs<OP>();
-  const int lane = threadIdx.x & 63, i = lane & 31, h = lane >> 5;
+// contract the group's NST stages: A rows at arow, B rows at brow (32 each);
+// bias: the A rows' sums too
+template <class OP, int NST, int NB>
+__device__ __forceinline__ void fuse_contract(const Stage<OP, NB>& stage, int arow, int brow, bool bias, f32x16& acc,
+                                              float& bsum) {
 #pragma unroll
   for (int q = 0; q < NST; ++q) {
-    const typename OP::S* st = stage + (size_t)q * SR * RS;
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
-      const typename OP::frag af = stage_get<OP>(st, arow0 + 32 * m + i, kk, h);
-      const typename OP::frag bf = stage_get<OP>(st, brow0 + 32 * n + i, kk, h);
-      if (n == 0) bsum = FragOps<OP>::sum(af, bsum);
+      const typename OP::frag af = stage.get(q, arow, kk);
+      const typename OP::frag bf = stage.get(q, brow, kk);
+      if (bias) bsum = FragOps<OP>::sum(af, bsum);
       acc = OP::mma(af, bf, acc);
     }
   }
@@ -595,8 +676,6 @@ __global__ __launch_bounds__(64 * WV) void k_flow_bwdw(const FlowDesc* __restric
   using S = typename OP::S;
   using frag = typename OP::frag;
   using FO = FragOps<OP>;
-  constexpr int SR = fuse_stage_rows(NB);
-  constexpr int RS = fuse_rs<OP>();
   constexpr int BS = 64 * WV;
   constexpr int T3 = 2 * NB, T = 2 * NB + 6;
   constexpr int OWN = (T + WV - 1) / WV;  // output tiles per wave
@@ -644,7 +723,7 @@ __global__ __launch_bounds__(64 * WV) void k_flow_bwdw(const FlowDesc* __restric
   // the lane's own LDS columns, BS apart: z_j at zc[j], its gradient at
   // zc[d + j], zero at zc[2 d], a sink for unused writes at zc[2 d + 1]
   float* zc = (float*)(flds + fuse_z_offset(L.fw_len, L.bw_len, L.bias_len, es)) + threadIdx.x;
-  S* stage = (S*)(flds + fuse_stage_offset(L.fw_len, L.bw_len, L.bias_len, es, d, BS));
+  const Stage<OP, NB> stage(flds, (unsigned)fuse_stage_offset(L.fw_len, L.bw_len, L.bias_len, es, d, BS), wave);
   copy16(sfw, fw + L.fw_off, L.fw_len * es);
   copy16(sbw, bw + L.bw_off, L.bw_len * es);
   copy16(sb, bias + L.bias_off, L.bias_len * 4);
@@ -680,7 +759,6 @@ __global__ __launch_bounds__(64 * WV) void k_flow_bwdw(const FlowDesc* __restric
   const frag* w3t = (const frag*)sbw;                       // [2][2 NB][32][2]
   const frag* w2t = (const frag*)(sbw + NB * 2048);         // [2][4][32][2]
   const frag* w1t = (const frag*)(sbw + NB * 2048 + 4096);  // [1][4][32][2]
-  S* mystage = stage + (size_t)wave * SR * RS;
   f32x16 acc[OWN];
   float bsum[OWN];
 #pragma unroll
@@ -733,14 +811,15 @@ __global__ __launch_bounds__(64 * WV) void k_flow_bwdw(const FlowDesc* __restric
     }
     // stage 1: [dlogit rows 0 .. 32 NB | h2 rows 32 NB .. 32 NB + 64]; dW3, db3
 #pragma unroll
-    for (int kk = 0; kk < 2 * NB; ++kk) stage_put<OP>(mystage, 32 * (kk >> 1), dlb[kk], kk & 1, s, h);
+    for (int kk = 0; kk < 2 * NB; ++kk) stage.put(32 * (kk >> 1), dlb[kk], kk & 1);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) stage_put<OP>(mystage, 32 * NB + 32 * (kk >> 1), h2b[kk], kk & 1, s, h);
+    for (int kk = 0; kk < 4; ++kk) stage.put(32 * NB + 32 * (kk >> 1), h2b[kk], kk & 1);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < OWN; ++k) {
       const int tau = wave + WV * k;
-      if (tau < T3) fuse_contract<OP, WV, SR>(stage, 0, 32 * NB, tau >> 1, tau & 1, acc[k], bsum[k]);
+      if (tau < T3)
+        fuse_contract<OP, WV, NB>(stage, 32 * (tau >> 1), 32 * NB + 32 * (tau & 1), (tau & 1) == 0, acc[k], bsum[k]);
     }
     __syncthreads();
     // dh2 = W3^T dlogit, masked by relu'; stage 2: [dpre2 rows 0 .. 64 | h1 rows 64 .. 128]
@@ -757,14 +836,15 @@ __global__ __launch_bounds__(64 * WV) void k_flow_bwdw(const FlowDesc* __restric
     }
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
-      stage_put<OP>(mystage, 32 * (kk >> 1), d2b[kk], kk & 1, s, h);
-      stage_put<OP>(mystage, 64 + 32 * (kk >> 1), h1b[kk], kk & 1, s, h);
+      stage.put(32 * (kk >> 1), d2b[kk], kk & 1);
+      stage.put(64 + 32 * (kk >> 1), h1b[kk], kk & 1);
     }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < OWN; ++k) {
       const int tau = wave + WV * k - T3;
-      if (tau >= 0 && tau < 4) fuse_contract<OP, WV, SR>(stage, 0, 64, tau >> 1, tau & 1, acc[k], bsum[k]);
+      if (tau >= 0 && tau < 4)
+        fuse_contract<OP, WV, NB>(stage, 32 * (tau >> 1), 64 + 32 * (tau & 1), (tau & 1) == 0, acc[k], bsum[k]);
     }
     __syncthreads();
     // dh1 = W2^T dpre2, masked; stage 3: [dpre1 rows 0 .. 64 | zA rows 64 .. 96, rows >= |A| zero]
@@ -780,17 +860,13 @@ __global__ __launch_bounds__(64 * WV) void k_flow_bwdw(const FlowDesc* __restric
       FO::mask(d1b[2 * to + 1], h1b[2 * to + 1]);
     }
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) stage_put<OP>(mystage, 32 * (kk >> 1), d1b[kk], kk & 1, s, h);
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const float val = (e < FAB && h == 0) ? za[e & (FAB - 1)] : 0.0f;
-      mystage[(64 + 16 * h + e) * RS + s] = OP::store(val);
-    }
+    for (int kk = 0; kk < 4; ++kk) stage.put(32 * (kk >> 1), d1b[kk], kk & 1);
+    stage.put_input(za);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < OWN; ++k) {
       const int tau = wave + WV * k - T3 - 4;
-      if (tau >= 0 && tau < 2) fuse_contract<OP, WV, SR>(stage, 0, 64, tau, 0, acc[k], bsum[k]);
+      if (tau >= 0 && tau < 2) fuse_contract<OP, WV, NB>(stage, 32 * tau, 64, true, acc[k], bsum[k]);
     }
     __syncthreads();
     // dzA = W1^T dpre1: rows a = 4h + r in registers 0..3
@@ -1151,7 +1227,7 @@ size_t fuse_lds_wv(const vgx_flow* f, int l, int wv) {
   const FlowLayerDesc& Ld = f->D.l[l];
   const int es = (int)sizeof(typename OP::S);
   return fuse_stage_offset(Ld.fw_len, Ld.bw_len, Ld.bias_len, es, f->dim, 64 * wv) +
-         (size_t)wv * fuse_stage_rows(Ld.nb) * fuse_rs<OP>() * es;
+         (size_t)wv * fuse_stage_bytes<OP>(Ld.nb);
 }
 
 // waves of the fused workgroup of layer l: eight (two per SIMD, so that one

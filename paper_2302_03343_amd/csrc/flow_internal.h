@@ -48,7 +48,6 @@ struct OpF32 {
 };
 
 typedef short s16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned u32x4v __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
@@ -90,12 +89,6 @@ struct FragOps<OpBF16> {
     }
     return acc;
   }
-  // (whole vectors are bit_cast, then indexed: a bit_cast of one element
-  // f[e] compiles to element 0)
-  static __device__ __forceinline__ unsigned short bits(const frag& f, int e) {
-    const u16x8 u = __builtin_bit_cast(u16x8, f);
-    return u[e];
-  }
 };
 
 template <>
@@ -114,7 +107,6 @@ struct FragOps<OpF32> {
     for (int e = 0; e < 8; ++e) acc += f[e];
     return acc;
   }
-  static __device__ __forceinline__ float bits(const frag& f, int e) { return f[e]; }
 };
 
 constexpr int FH = 64;       // hidden width
