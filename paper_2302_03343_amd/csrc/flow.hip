@@ -42,8 +42,9 @@
 
 namespace vgx {
 
-template <int NBM, int MODE, class OP>
-__global__ __launch_bounds__(FWD_BLOCK) void k_flow_fwd(const FlowDesc* __restrict__ Dp, FwdArgs a,
+// BS threads share one LDS copy of the weights (FWD_BLOCK, or FWD_WIDE).
+template <int NBM, int MODE, int BS, class OP>
+__global__ __launch_bounds__(BS) void k_flow_fwd(const FlowDesc* __restrict__ Dp, FwdArgs a,
                                                      const typename OP::S* __restrict__ fw,
                                                      const float* __restrict__ bias) {
   using S = typename OP::S;
@@ -59,7 +60,7 @@ __global__ __launch_bounds__(FWD_BLOCK) void k_flow_fwd(const FlowDesc* __restri
   __syncthreads();
   const int lane = threadIdx.x & 63;
   const int wave = (threadIdx.x >> 6) * gridDim.x + blockIdx.x;
-  const int nwaves = gridDim.x * (FWD_BLOCK / 64);
+  const int nwaves = gridDim.x * (BS / 64);
   const int64_t ntiles = (a.n + 63) / 64;  // tile pairs
   const int d = D.d;
   Comp sr, sg;
@@ -67,15 +68,15 @@ __global__ __launch_bounds__(FWD_BLOCK) void k_flow_fwd(const FlowDesc* __restri
     const int64_t i = t * 64 + lane;  // the lane's own sample
     const bool valid = i < a.n;
     if (MODE == 2) {
-      flow_draw(z, d, i, a.it, a.sid, a.k0, a.k1);
+      flow_draw<BS>(z, d, i, a.it, a.sid, a.k0, a.k1);
     } else {
-      for (int j = 0; j < d; ++j) z[j * FWD_BLOCK] = valid ? (float)a.yin[(int64_t)j * a.n + i] : 0.5f;
+      for (int j = 0; j < d; ++j) z[j * BS] = valid ? (float)a.yin[(int64_t)j * a.n + i] : 0.5f;
     }
-    const double lq = flow_layers<MODE == 2, OP>(D, sfw, sb, z, i, valid, MODE == 1 ? a.zsave : nullptr, a.n);
+    const double lq = flow_layers<MODE == 2, OP, BS>(D, sfw, sb, z, i, valid, MODE == 1 ? a.zsave : nullptr, a.n);
     if (valid) {
       a.logq[i] = lq;
       if (a.out) {
-        for (int j = 0; j < d; ++j) a.out[(int64_t)j * a.n + i] = (double)z[j * FWD_BLOCK];
+        for (int j = 0; j < d; ++j) a.out[(int64_t)j * a.n + i] = (double)z[j * BS];
       }
       if (MODE == 1) {
         const double gi = a.g[i];
@@ -87,14 +88,14 @@ __global__ __launch_bounds__(FWD_BLOCK) void k_flow_fwd(const FlowDesc* __restri
     }
   }
   if (MODE == 1) {
-    __shared__ double red[4][FWD_BLOCK / 64];
+    __shared__ double red[4][BS / 64];
     const double v0 = wave_sum(sr.s), v1 = wave_sum(sr.c), v2 = wave_sum(sg.s), v3 = wave_sum(sg.c);
     const int wv = threadIdx.x >> 6;
     if (lane == 0) { red[0][wv] = v0; red[1][wv] = v1; red[2][wv] = v2; red[3][wv] = v3; }
     __syncthreads();
     if (threadIdx.x < 4) {
       double acc = 0.0;
-      for (int k = 0; k < FWD_BLOCK / 64; ++k) acc += red[threadIdx.x][k];
+      for (int k = 0; k < BS / 64; ++k) acc += red[threadIdx.x][k];
       a.partials[blockIdx.x * 4 + threadIdx.x] = acc;
     }
   }
@@ -1282,11 +1283,11 @@ vgx_status fuse_allow_lds() {
 // the backward of layers with |B| <= 4 runs fused with its weight gradients
 bool fused_backward(const vgx_flow* f) { return f->nbm <= 4; }
 
-size_t fwd_lds_es(const vgx_flow* f, int es) {
-  return fwd_z_offset(f->D.fw_total, f->D.bias_total, es) + sizeof(float) * (size_t)f->dim * FWD_BLOCK;
+size_t fwd_lds_es(const vgx_flow* f, int es, int bs = FWD_BLOCK) {
+  return fwd_z_offset(f->D.fw_total, f->D.bias_total, es) + sizeof(float) * (size_t)f->dim * bs;
 }
 
-size_t fwd_lds(const vgx_flow* f) { return fwd_lds_es(f, op_es(f)); }
+size_t fwd_lds(const vgx_flow* f, int bs = FWD_BLOCK) { return fwd_lds_es(f, op_es(f), bs); }
 
 vgx_status pack(vgx_flow* f) {
   const int tot = f->D.fw_total > f->D.bw_total ? f->D.fw_total : f->D.bw_total;
@@ -1316,9 +1317,13 @@ vgx_status set_lds_limits(size_t fwd, size_t bwd, size_t wgr, size_t fus) {
   cur_w = wgr;
   cur_u = fus;
   if (fus > 0) VGX_TRY(fuse_allow_lds<OP>());
-  VGX_HIP(hipFuncSetAttribute((const void*)k_flow_fwd<NB, 0, OP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd));
-  VGX_HIP(hipFuncSetAttribute((const void*)k_flow_fwd<NB, 1, OP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd));
-  VGX_HIP(hipFuncSetAttribute((const void*)k_flow_fwd<NB, 2, OP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd));
+  VGX_HIP(hipFuncSetAttribute((const void*)k_flow_fwd<NB, 0, FWD_BLOCK, OP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd));
+  VGX_HIP(hipFuncSetAttribute((const void*)k_flow_fwd<NB, 1, FWD_BLOCK, OP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd));
+  VGX_HIP(hipFuncSetAttribute((const void*)k_flow_fwd<NB, 2, FWD_BLOCK, OP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd));
+  if constexpr (sizeof(typename OP::S) == 2) {  // a launch asks only for what its flow needs
+    VGX_HIP(hipFuncSetAttribute((const void*)k_flow_fwd<NB, 0, FWD_WIDE, OP>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+    VGX_HIP(hipFuncSetAttribute((const void*)k_flow_fwd<NB, 2, FWD_WIDE, OP>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+  }
   if constexpr (NB > 4) {
     VGX_HIP(hipFuncSetAttribute((const void*)k_flow_bwd<NB, OP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bwd));
     VGX_HIP(hipFuncSetAttribute((const void*)k_flow_wgrad<NB, OP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)wgr));
@@ -1360,18 +1365,34 @@ int fwd_grid(const vgx_flow* f, int64_t n, int per_cu = 2) {
   return (int)(g < 1 ? 1 : g);
 }
 
-template <int MODE, class OP>
-vgx_status launch_fwd_op(vgx_flow* f, int grid, const FwdArgs& a, hipStream_t st) {
-  const size_t lds = fwd_lds(f);
+template <int MODE, int BS, class OP>
+vgx_status launch_fwd_bs(vgx_flow* f, int grid, const FwdArgs& a, hipStream_t st) {
+  const size_t lds = fwd_lds(f, BS);
   const typename OP::S* fw = (const typename OP::S*)f->fw;
-#define L_(NB)                                                                                                  \
-  case NB:                                                                                                      \
-    hipLaunchKernelGGL((k_flow_fwd<NB, MODE, OP>), dim3(grid), dim3(FWD_BLOCK), lds, st, f->d_desc, a, fw, f->bias); \
+#define L_(NB)                                                                                                     \
+  case NB:                                                                                                         \
+    hipLaunchKernelGGL((k_flow_fwd<NB, MODE, BS, OP>), dim3(grid), dim3(BS), lds, st, f->d_desc, a, fw, f->bias); \
     break;
   switch (f->nbm) { L_(1) L_(2) L_(4) L_(8) default: set_error("flow: bad |B| bound"); return VGX_EINVAL; }
 #undef L_
   VGX_HIP(hipGetLastError());
   return VGX_OK;
+}
+
+// Sampling and density take 153 registers, so three waves fit on a SIMD, but
+// of two workgroups of eight waves only one: large batches (more than one
+// tile pair per wave of one such workgroup per CU) run with twelve waves,
+// one workgroup per CU, where the LDS holds their columns (sampling 140000
+// points 28.0 -> 26.1 us at d = 3 and 56.6 -> 47.8 at d = 8; 1e6 points 124.2 ->
+// 121.3 and 249 -> 226).  The training forward takes 201 registers: eight waves.
+template <int MODE, class OP>
+vgx_status launch_fwd_op(vgx_flow* f, int grid, const FwdArgs& a, hipStream_t st) {
+  if constexpr (MODE != 1 && sizeof(typename OP::S) == 2) {
+    const int64_t pairs = (a.n + 63) / 64;
+    if (pairs > (int64_t)device_cus() * (FWD_BLOCK / 64) && fwd_lds(f, FWD_WIDE) <= 160 * 1024)
+      return launch_fwd_bs<MODE, FWD_WIDE, OP>(f, device_cus(), a, st);
+  }
+  return launch_fwd_bs<MODE, FWD_BLOCK, OP>(f, grid, a, st);
 }
 
 template <int MODE>

@@ -116,6 +116,7 @@ constexpr int FAB = 8;       // max |A|, |B|
 constexpr int FDM = VGX_MAX_DIM;
 constexpr int FBLOCK = 256;
 constexpr int FWD_BLOCK = 512;  // forward kernels: 8 waves share one LDS copy of the weights
+constexpr int FWD_WIDE = 768;   // or 12 (large batches)
 
 struct FlowLayerDesc {
   int na, nb;
