@@ -104,35 +104,13 @@ __global__ __launch_bounds__(BS) void k_flow_fwd(const FlowDesc* __restrict__ Dp
 // loss L = sum r / sum g^2, scale = -1/sum g^2 and the ok flag from the
 // forward's partial rows [rows][4], by one wave (every lane gets them):
 // lane l sums rows l, l + 64, ... (compensated), then the lanes combine in a
-// fixed butterfly order and lane 0's totals are broadcast.  The loads of the
-// first 512 rows are issued apart (loss_load), so that other work can run
-// while they are in flight.
-struct LossRows {
-  double v[8][4];
-};
-
-__device__ __forceinline__ void loss_load(const double* __restrict__ partials, int rows, int r0, LossRows& lr) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const int r = r0 + 64 * k + lane;
-#pragma unroll
-    for (int col = 0; col < 4; ++col) lr.v[k][col] = r < rows ? partials[r * 4 + col] : 0.0;
-  }
-}
-
-__device__ __forceinline__ void loss_finish(const double* __restrict__ partials, int rows, LossRows& lr,
-                                            double (&out)[3]) {
+// fixed butterfly order and lane 0's totals are broadcast.
+__device__ __forceinline__ void loss_reduce(const double* __restrict__ partials, int rows, double (&out)[3]) {
   const int lane = threadIdx.x & 63;
   Comp c[4];
-  for (int r0 = 0; r0 < rows; r0 += 8 * 64) {
-    if (r0 > 0) loss_load(partials, rows, r0, lr);
+  for (int r = lane; r < rows; r += 64) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
-      if (r0 + 64 * k + lane < rows) {
-#pragma unroll
-        for (int col = 0; col < 4; ++col) c[col].add(lr.v[k][col]);
-      }
+    for (int col = 0; col < 4; ++col) c[col].add(partials[r * 4 + col]);
   }
   double tot[4];
 #pragma unroll
@@ -150,12 +128,6 @@ __device__ __forceinline__ void loss_finish(const double* __restrict__ partials,
   out[0] = L;
   out[1] = -1.0 / sg;
   out[2] = (isfinite(L) && sg > 0.0) ? 1.0 : 0.0;
-}
-
-__device__ __forceinline__ void loss_reduce(const double* __restrict__ partials, int rows, double (&out)[3]) {
-  LossRows lr;
-  loss_load(partials, rows, 0, lr);
-  loss_finish(partials, rows, lr, out);
 }
 
 __global__ __launch_bounds__(64) void k_flow_loss(const double* __restrict__ partials, int rows, double* __restrict__ out) {
@@ -668,6 +640,20 @@ __device__ __forceinline__ void fuse_contract(const Stage<OP, NB>& stage, int ar
   }
 }
 
+// The lanes' compensated sums merged in a fixed order, the total in lane 63.
+__device__ __forceinline__ void wave_comp(Comp& v) {
+  auto step = [&](double s, double c) {
+    v.add(s);
+    v.c += c;
+  };
+  step(dpp_get<0x111>(v.s), dpp_get<0x111>(v.c));  // row_shr:1, 2, 4, 8
+  step(dpp_get<0x112>(v.s), dpp_get<0x112>(v.c));
+  step(dpp_get<0x114>(v.s), dpp_get<0x114>(v.c));
+  step(dpp_get<0x118>(v.s), dpp_get<0x118>(v.c));
+  step(dpp_get<0x142, 0xA>(v.s), dpp_get<0x142, 0xA>(v.c));  // row_bcast15
+  step(dpp_get<0x143, 0xC>(v.s), dpp_get<0x143, 0xC>(v.c));  // row_bcast31
+}
+
 template <int NB, int WV, class OP>
 __global__ __launch_bounds__(64 * WV) void k_flow_bwdw(const FlowDesc* __restrict__ Dp, BwdArgs a,
                                                      const typename OP::S* __restrict__ fw,
@@ -712,11 +698,13 @@ __global__ __launch_bounds__(64 * WV) void k_flow_bwdw(const FlowDesc* __restric
     const double rv = a.rsave[ic];
     pr = ok ? rv : 0.0;
   };
-  // the loss scale: reduced by every wave from the forward's partial rows
+  // the loss scale: reduced by every workgroup from the forward's partial rows
   // (first launch of a step; workgroup 0 stores the loss), else read; the
-  // rows' loads are in flight while the packs are copied
-  LossRows lrows;
-  if (a.partials) loss_load(a.partials, a.prows, 0, lrows);
+  // first rows' loads are in flight while the packs are copied.  The rows
+  // are split over the waves (by every wave for itself this launch took 31 us, now 28.7).
+  const double4* prow = (const double4*)a.partials;
+  double4 pv{0.0, 0.0, 0.0, 0.0};
+  if (prow && (int)threadIdx.x < a.prows) pv = prow[threadIdx.x];
   if (n > 0) fetch(blockIdx.x);
   S* sfw = (S*)flds;
   S* sbw = sfw + L.fw_len;
@@ -724,7 +712,9 @@ __global__ __launch_bounds__(64 * WV) void k_flow_bwdw(const FlowDesc* __restric
   // the lane's own LDS columns, BS apart: z_j at zc[j], its gradient at
   // zc[d + j], zero at zc[2 d], a sink for unused writes at zc[2 d + 1]
   float* zc = (float*)(flds + fuse_z_offset(L.fw_len, L.bw_len, L.bias_len, es)) + threadIdx.x;
-  const Stage<OP, NB> stage(flds, (unsigned)fuse_stage_offset(L.fw_len, L.bw_len, L.bias_len, es, d, BS), wave);
+  const unsigned stage_off = (unsigned)fuse_stage_offset(L.fw_len, L.bw_len, L.bias_len, es, d, BS);
+  const Stage<OP, NB> stage(flds, stage_off, wave);
+  double* red = (double*)(flds + stage_off);  // the waves' sums [WV][4], before the stages are in use
   copy16(sfw, fw + L.fw_off, L.fw_len * es);
   copy16(sbw, bw + L.bw_off, L.bw_len * es);
   copy16(sb, bias + L.bias_off, L.bias_len * 4);
@@ -742,20 +732,46 @@ __global__ __launch_bounds__(64 * WV) void k_flow_bwdw(const FlowDesc* __restric
   float* zbp[NB];
 #pragma unroll
   for (int jb = 0; jb < NB; ++jb) zbp[jb] = zc + L.b_idx[jb] * BS;
-  double scale;
-  if (a.partials) {
-    double lv[3];
-    loss_finish(a.partials, a.prows, lrows, lv);
-    scale = lv[1];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      a.loss_out[0] = lv[0];
-      a.loss_out[1] = lv[1];
-      a.loss_out[2] = lv[2];
+  if (prow) {
+    Comp c[2];
+    for (int r = threadIdx.x; r < a.prows; r += BS) {
+      if (r >= BS) pv = prow[r];
+      c[0].add(pv.x);
+      c[0].add(pv.y);
+      c[1].add(pv.z);
+      c[1].add(pv.w);
     }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      wave_comp(c[q]);
+      if (lane == 63) {
+        red[4 * wave + 2 * q] = c[q].s;
+        red[4 * wave + 2 * q + 1] = c[q].c;
+      }
+    }
+  }
+  __syncthreads();
+  double scale;
+  if (prow) {
+    Comp c[2];
+#pragma unroll
+    for (int k = 0; k < WV; ++k)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        c[q].add(red[4 * k + 2 * q]);
+        c[q].c += red[4 * k + 2 * q + 1];
+      }
+    const double sr = c[0].value(), sg = c[1].value(), loss = sr / sg;
+    scale = -1.0 / sg;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      a.loss_out[0] = loss;
+      a.loss_out[1] = scale;
+      a.loss_out[2] = (isfinite(loss) && sg > 0.0) ? 1.0 : 0.0;
+    }
+    __syncthreads();  // red has been read
   } else {
     scale = a.loss[1];
   }
-  __syncthreads();
   const LayerLds<OP> W = layer_lds<OP>(sfw, sb, L, L.fw_off, L.bias_off);
   const frag* w3t = (const frag*)sbw;                       // [2][2 NB][32][2]
   const frag* w2t = (const frag*)(sbw + NB * 2048);         // [2][4][32][2]
