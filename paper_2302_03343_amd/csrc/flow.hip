@@ -510,9 +510,10 @@ template <class OP>
 __device__ __forceinline__ void mlp_hidden_fb(const float (&za)[FAB], const LayerLds<OP>& W, typename OP::frag (&h1b)[4],
                                               typename OP::frag (&h2b)[4]) {
   const int lane = threadIdx.x & 63, i = lane & 31, h = lane >> 5;
-  typename OP::frag bz;
+  f32x8 zx;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) OP::set(bz, e, h == 0 ? za[e] : 0.0f);
+  for (int e = 0; e < 8; ++e) zx[e] = h == 0 ? za[e] : 0.0f;
+  const typename OP::frag bz = OP::pack(zx);
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     const f32x16 p = OP::mma(W.w1p[(t * 32 + i) * 2 + h], bz, bias_tile(W.b1 + 32 * t, h));
@@ -573,10 +574,10 @@ struct Stage<OpBF16, NB> {
   // the network's input za as rows 64 .. 96 (zero beyond |A|)
   __device__ __forceinline__ void put_input(const float (&za)[FAB]) const {
     const int lane = threadIdx.x & 63, s = lane & 31, h = lane >> 5;
-    frag f;
+    f32x8 zx;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) OpBF16::set(f, e, h == 0 ? za[e] : 0.0f);
-    const u32x4v v = __builtin_bit_cast(u32x4v, f);
+    for (int e = 0; e < 8; ++e) zx[e] = h == 0 ? za[e] : 0.0f;
+    const u32x4v v = __builtin_bit_cast(u32x4v, OpBF16::pack(zx));
     const unsigned b = z0 + ((stage_swizzle(s) ^ (4 * h)) << 3);  // h = 0: rows 64 .. 80, h = 1: 80 .. 96
     put8(b, 16, v[0], v[1]);
     put8(b, 17, v[2], v[3]);

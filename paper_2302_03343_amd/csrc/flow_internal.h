@@ -10,6 +10,9 @@ namespace vgx {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4v __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 // Operand precision of the networks' matrix products.  OpBF16 is the
 // product path (v_mfma_f32_32x32x16_bf16).  OpF32 is a validation build of
@@ -25,7 +28,18 @@ struct OpBF16 {
   static __device__ __forceinline__ f32x16 mma(const frag& a, const frag& b, const f32x16& c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
   }
-  static __device__ __forceinline__ void set(frag& f, int e, float x) { f[e] = (__bf16)x; }
+  // eight values as an operand, two per v_cvt_pk_bf16_f32 (converted one at a
+  // time, each took an instruction and each pair a v_perm to join)
+  static __device__ __forceinline__ frag pack(const f32x8& x) {
+    unsigned r[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const f32x2 v = {x[2 * k], x[2 * k + 1]};
+      r[k] = __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+    }
+    const u32x4v u = {r[0], r[1], r[2], r[3]};
+    return __builtin_bit_cast(frag, u);
+  }
   static __device__ __forceinline__ float get(const frag& f, int e) { return (float)f[e]; }
   static __device__ __forceinline__ S store(float x) {
     const __bf16 b = (__bf16)x;
@@ -42,14 +56,12 @@ struct OpF32 {
     for (int e = 0; e < 8; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], c, 0, 0, 0);
     return c;
   }
-  static __device__ __forceinline__ void set(frag& f, int e, float x) { f[e] = x; }
+  static __device__ __forceinline__ frag pack(const f32x8& x) { return x; }
   static __device__ __forceinline__ float get(const frag& f, int e) { return f[e]; }
   static __device__ __forceinline__ S store(float x) { return x; }
 };
 
 typedef short s16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned u32x4v __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 // ReLU, ReLU-derivative mask and element sum of an operand fragment.
 template <class OP>
@@ -150,10 +162,10 @@ __device__ __forceinline__ f32x16 zero16() {
 // 8 consecutive accumulator registers as a B operand (K step half 0 or 1).
 template <class OP>
 __device__ __forceinline__ typename OP::frag to_b(const f32x16& c, int half) {
-  typename OP::frag r;
+  f32x8 x;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) OP::set(r, e, half ? c[8 + e] : c[e]);
-  return r;
+  for (int e = 0; e < 8; ++e) x[e] = half ? c[8 + e] : c[e];
+  return OP::pack(x);
 }
 
 // row (feature / bin) held by register v of lane half h in a 32x32 D tile
@@ -230,9 +242,10 @@ template <int NBM, class OP>
 __device__ __forceinline__ void mlp_fwd(const float (&za)[FAB], int na, int nb, const LayerLds<OP>& W, f32x16 (&h1)[2],
                                         f32x16 (&h2)[2], f32x16 (&lg)[NBM]) {
   const int lane = threadIdx.x & 63, i = lane & 31, h = lane >> 5;
-  typename OP::frag bz;
+  f32x8 zx;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) OP::set(bz, e, (h == 0 && e < na) ? za[e] : 0.0f);
+  for (int e = 0; e < 8; ++e) zx[e] = (h == 0 && e < na) ? za[e] : 0.0f;
+  const typename OP::frag bz = OP::pack(zx);
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     h1[t] = OP::mma(W.w1p[(t * 32 + i) * 2 + h], bz, bias_tile(W.b1 + 32 * t, h));
@@ -268,9 +281,10 @@ template <class OP>
 __device__ __forceinline__ void mlp_hidden(const float (&za)[FAB], int na, const LayerLds<OP>& W,
                                            typename OP::frag (&h2b)[4]) {
   const int lane = threadIdx.x & 63, i = lane & 31, h = lane >> 5;
-  typename OP::frag bz;
+  f32x8 zx;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) OP::set(bz, e, (h == 0 && e < na) ? za[e] : 0.0f);
+  for (int e = 0; e < 8; ++e) zx[e] = (h == 0 && e < na) ? za[e] : 0.0f;
+  const typename OP::frag bz = OP::pack(zx);
   typename OP::frag h1b[4];
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
