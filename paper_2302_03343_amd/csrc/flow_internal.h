@@ -325,11 +325,16 @@ __device__ __forceinline__ f32x16 mlp_logits(const typename OP::frag (&h2b)[4], 
 constexpr float FLOG2E = 1.44269504088896341f;
 __device__ __forceinline__ float exp_shifted(float x, float nml) { return __builtin_amdgcn_exp2f(fmaf(x, FLOG2E, nml)); }
 
+// Maximum that keeps a NaN (as the sum of the exponentials does anyway): two
+// of them are one v_maximum3_f32, where fmaxf first quiets each operand, one
+// instruction per value.
+__device__ __forceinline__ float max_nan(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+
 __device__ __forceinline__ float softexp32(f32x16& q) {
-  float m = q[0];
+  float m = max_nan(q[0], q[1]);
 #pragma unroll
-  for (int v = 1; v < 16; ++v) m = fmaxf(m, q[v]);
-  m = fmaxf(m, xor32(m));
+  for (int v = 2; v < 16; v += 2) m = max_nan(max_nan(m, q[v]), q[v + 1]);
+  m = max_nan(m, xor32(m));
   const float nml = -m * FLOG2E;
   float s = 0.0f;
 #pragma unroll
@@ -464,9 +469,9 @@ __device__ __forceinline__ void pair_swap(f32x16& a, f32x16& b) {
 // in place: exponentials of the lane's 32 logits less their maximum; returns
 // their sum (unnormalised softmax)
 __device__ __forceinline__ float softexp_own(f32x16& lo, f32x16& hi) {
-  float m = fmaxf(lo[0], hi[0]);
+  float m = max_nan(lo[0], hi[0]);
 #pragma unroll
-  for (int v = 1; v < 16; ++v) m = fmaxf(m, fmaxf(lo[v], hi[v]));
+  for (int v = 1; v < 16; ++v) m = max_nan(max_nan(m, lo[v]), hi[v]);
   const float nml = -m * FLOG2E;
   float s = 0.0f;
 #pragma unroll
