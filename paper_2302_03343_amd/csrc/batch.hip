@@ -388,6 +388,15 @@ vgx_status autotune(vgx_batch* b, int fixed_tile, int fixed_block) {
 
 }  // namespace
 
+// Waits for what a context's own stream still has to do on its grid,
+// histogram and records, before the batch's stream touches them.
+static vgx_status join_stream(const vgx_batch* b, vgx_vegas* c) {
+  if (!c->tail || c->stream == b->stream) return VGX_OK;
+  VGX_HIP(hipStreamSynchronize(c->stream));
+  c->tail = false;
+  return VGX_OK;
+}
+
 extern "C" vgx_status batch_create(vgx_vegas* const* ctxs, int32_t count, const int64_t* n_samples, int32_t tile,
                                    int32_t block, void* stream, vgx_batch** out) {
   VGX_CHECK(out && ctxs && n_samples, "batch_create: null argument");
@@ -449,7 +458,8 @@ extern "C" vgx_status batch_create(vgx_vegas* const* ctxs, int32_t count, const 
   if (s != VGX_OK) { batch_destroy(b); return s; }
   hipError_t e = hipMemsetAsync(b->d_state, 0, state_bytes(count), b->stream);
   if (e != hipSuccess) { s = hip_fail(e, "batch_create", __FILE__, __LINE__); batch_destroy(b); return s; }
-  s = autotune(b, tile, block);
+  for (int k = 0; k < count && s == VGX_OK; ++k) s = join_stream(b, ctxs[k]);  // the tuning reads the grids
+  if (s == VGX_OK) s = autotune(b, tile, block);
   if (s == VGX_OK) s = upload_items(b, b->stream);
   if (s == VGX_OK) {
     e = hipStreamSynchronize(b->stream);
@@ -480,12 +490,8 @@ extern "C" vgx_status batch_iterate(vgx_batch* b, int32_t iteration, vgx_iter_re
   int* krec = batch_krec(b->pinned_state);
   for (int k = 0; k < b->count; ++k) {
     if (b->ctx[k]->n_rec >= MAX_RECORDS) { set_error("batch_iterate: context %d has too many records", k); return VGX_ESTATE; }
-    if (b->ctx[k]->pend_k >= 0 || (b->ctx[k]->tail && b->ctx[k]->stream != b->stream)) {
-      // a record left pending, or a histogram still being written, on the context's own stream
-      VGX_TRY(vegas_flush_pending(b->ctx[k]));
-      VGX_HIP(hipStreamSynchronize(b->ctx[k]->stream));
-    }
-    b->ctx[k]->tail = false;
+    VGX_TRY(vegas_flush_pending(b->ctx[k]));
+    VGX_TRY(join_stream(b, b->ctx[k]));
     krec[k] = b->ctx[k]->n_rec;
   }
   b->pinned_state->tile_counter = 0;

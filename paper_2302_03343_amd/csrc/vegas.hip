@@ -1154,6 +1154,7 @@ vgx_status launch_reduce(vgx_vegas* v, int rows, int ncols, int64_t n, bool defe
   VGX_CHECK(rows >= 1 && rows <= RMAXROWS, "reduce: %d partial rows (1..%d)", rows, RMAXROWS);
   VGX_CHECK(v->pend_k < 0, "reduce: record %d is still pending", v->pend_k);
   const int blocks = (ncols + RCOLS - 1) / RCOLS;
+  v->tail = true;
   HostOut host{};
   if (!defer) host = {v->host()->rec, &v->host()->comb, &v->host()->flag, ++v->seq};
   hipLaunchKernelGGL(k_reduce, dim3(blocks), dim3(RBLOCK), 0, v->stream, v->partials, rows, v->pstride, ncols,
@@ -1224,7 +1225,6 @@ bool host_flag(const vgx_vegas* v) {
 
 vgx_status read_record(vgx_vegas* v, int k, vgx_iter_result* out, RecordKind kind) {
   if (!host_flag(v)) VGX_HIP(hipStreamSynchronize(v->stream));
-  v->tail = true;
   const IterRecord* h = v->host()->rec + k;
   const Combined* hc = &v->host()->comb;
   v->comb_fresh = true;
@@ -1254,6 +1254,7 @@ vgx_status read_record(vgx_vegas* v, int k, vgx_iter_result* out, RecordKind kin
 
 vgx_status vegas_flush_pending(vgx_vegas* v) {
   if (v->pend_k < 0) return VGX_OK;
+  v->tail = true;
   hipLaunchKernelGGL(k_finalize, dim3(1), dim3(64), 0, v->stream, v->rec, v->pend_k, v->pend_n, v->comb);
   VGX_HIP(hipGetLastError());
   v->pend_k = -1;
@@ -1352,6 +1353,7 @@ extern "C" vgx_status vegas_refine(vgx_vegas* v) {
   VGX_CHECK(v, "vegas_refine: null context");
   if (!v->have_hist) { set_error("vegas_refine: no histogram (run vegas_iterate first)"); return VGX_ESTATE; }
   const int kp = v->pend_k;
+  v->tail = true;
   hipLaunchKernelGGL(k_refine, dim3(v->dim + (kp >= 0 ? 1 : 0)), dim3(64), 0, v->stream, v->edges, v->bins, v->hist,
                      v->nb, v->alpha, v->rec, kp, v->pend_n, v->comb);
   VGX_HIP(hipGetLastError());
@@ -1430,8 +1432,8 @@ extern "C" vgx_status vegas_set_grid(vgx_vegas* v, const double* edges) {
   double* h = v->host()->grid;
   VGX_HIP(hipStreamSynchronize(v->stream));  // an earlier copy from h may be under way
   memcpy(h, edges, bytes);
-  VGX_HIP(upload_grid(v));
   v->tail = true;
+  VGX_HIP(upload_grid(v));
   return VGX_OK;
 }
 

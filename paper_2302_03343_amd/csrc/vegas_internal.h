@@ -385,7 +385,7 @@ struct vgx_vegas {
   void* pinned = nullptr;           // host memory the device writes: PinnedHost
   int n_rec = 0;
   bool rec_host = true;             // the host mirror holds every record
-  bool tail = false;                // the stream may still be writing the histogram of a record read, or a grid set
+  bool tail = false;                // work on the grid, histogram or records was enqueued since the stream was waited for
   unsigned long long seq = 0;       // records read back through the mirror's flag
   bool comb_fresh = false;           // the host copy of the combination (in pinned) is current
   int pend_k = -1;                  // record holding only S1, S2 until the next refinement completes it (< 0: none)
