@@ -31,13 +31,10 @@ struct Combined {
 constexpr int MAX_RECORDS = 4096;
 
 // Where a kernel leaves a completed record for the host: pinned host memory
-// mirroring the records and the combination, and a word that takes `seq` once
-// both are visible there.  flag null: the device copies only.
+// mirroring the records and the combination.  Null: the device copies only.
 struct HostOut {
   IterRecord* rec;
   Combined* comb;
-  unsigned long long* flag;
-  unsigned long long seq;
 };
 
 // Grid map (inverse transform through the piecewise-constant density of the
@@ -182,7 +179,7 @@ __device__ __forceinline__ Comp wave_merge(Comp a, int lanes) {
 // estimate exact (sigma 0).  Called by the 64 lanes of one wave, which split
 // the records (lane l takes l, l+64, ...) so that the cost per iteration does
 // not grow with the number of stored estimates; lane 0 writes the results,
-// with host.flag set also to the host.
+// with host.rec set also to the host.
 __device__ inline void finalize_record(double s1, double s2, int64_t n, IterRecord* rec, int k_rec, Combined* comb,
                                        const HostOut& host = {}) {
   // no contraction into FMAs, so that every kernel that inlines this gives the same bits
@@ -256,11 +253,9 @@ __device__ inline void finalize_record(double s1, double s2, int64_t n, IterReco
   }
   if (lane == 0) {
     *comb = c;
-    if (host.flag) {
+    if (host.rec) {
       host.rec[k_rec] = r;
       *host.comb = c;
-      __threadfence_system();
-      __hip_atomic_store(host.flag, host.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
   }
 }
@@ -353,7 +348,6 @@ __device__ inline void refine_dim(double* __restrict__ ej, double2* __restrict__
 struct PinnedHost {
   IterRecord rec[MAX_RECORDS];
   Combined comb;
-  unsigned long long flag;
   double grid[1];
 };
 
@@ -386,7 +380,6 @@ struct vgx_vegas {
   int n_rec = 0;
   bool rec_host = true;             // the host mirror holds every record
   bool tail = false;                // work on the grid, histogram or records was enqueued since the stream was waited for
-  unsigned long long seq = 0;       // records read back through the mirror's flag
   bool comb_fresh = false;           // the host copy of the combination (in pinned) is current
   int pend_k = -1;                  // record holding only S1, S2 until the next refinement completes it (< 0: none)
   int64_t pend_n = 0;               // its sample count
