@@ -681,7 +681,7 @@ hipError_t allow_lds() {
 
 // The tables of the interpolation with the grid in LDS (sync): uploaded, and
 // member 0's nodes regrouped on the device.
-vgx_status setup_lds(vgx_pdf* p, const double* lx, const double* lq, hipStream_t st) {
+vgx_status setup_lds(vgx_pdf* p, hipStream_t st) {
   PdfLdsArgs a{};
   if (!pdf_lds_plan(p, a)) return VGX_OK;
   const int n_nodes = p->n_x * p->q_off[p->n_sub];
@@ -692,7 +692,7 @@ vgx_status setup_lds(vgx_pdf* p, const double* lx, const double* lq, hipStream_t
   p->lds_o_n32 = p->lds_o_n64 + (size_t)g64 * a.node_bytes;
   unsigned char* h = (unsigned char*)malloc(p->lds_o_n64);
   if (!h) { set_error("pdf_create: host allocation failed"); return VGX_ENOMEM; }
-  pdf_lds_fill(p, a, lx, lq, h, (double*)(h + p->lds_o_ratios));
+  pdf_lds_fill(p, a, h, (double*)(h + p->lds_o_ratios));
   vgx_status s = dev_alloc((void**)&p->lds_block, p->lds_o_n32 + (size_t)g32 * a.node_bytes);
   if (s == VGX_OK) {
     hipError_t e = hipMemcpyAsync(p->lds_block, h, p->lds_o_n64, hipMemcpyHostToDevice, st);
@@ -824,7 +824,7 @@ extern "C" vgx_status pdf_create_set(const vgx_pdf_desc* d, int32_t n_members, v
     if (e == hipSuccess) e = hipMemsetAsync(p->oor, 0, sizeof(unsigned long long), st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) st_ = hip_fail(e, "pdf_create copies", __FILE__, __LINE__);
-    if (st_ == VGX_OK) st_ = setup_lds(p, lx, lq, st);
+    if (st_ == VGX_OK) st_ = setup_lds(p, st);
   } while (0);
   free(lx); free(lq); free(v); free(v32);
   if (st_ != VGX_OK) { pdf_destroy(p); return st_; }
