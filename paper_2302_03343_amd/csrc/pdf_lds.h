@@ -326,7 +326,7 @@ inline int pdf_host_cell(const double* knot, int n, double v) {
 // nodes), the windows need four knots per axis, start cells are bytes.
 inline bool pdf_lds_plan(const vgx_pdf* p, PdfLdsArgs& a) {
   const int nx = p->n_x, nq = p->q_off[p->n_sub];
-  const double tiny = 1e-290, huge = 1e290;  // 1/v is finite and normal
+  const double tiny = 1e-150, huge = 1e150;  // 1/v is finite and normal, as is v/v_i in a cell however wide
   if (p->h_x[0] < tiny || p->h_x[nx - 1] > huge || p->h_q2[0] < tiny || p->h_q2[nq - 1] > huge) return false;
   if (nx < 4 || nq < 4 || nx > kMaxLdsKnots || nq > kMaxLdsKnots) return false;
   auto up16 = [](int b) { return (b + 15) & ~15; };
