@@ -180,7 +180,7 @@ struct MinWaves<F, std::void_t<decltype(F::kMinWaves)>> { static constexpr int v
 // Caller points (flow samples) carry a density and an index into memory:
 // the integrand's occupancy bound would make those kernels spill, so they
 // take none.
-template <int D, class F, class Src, bool HIST, bool WIDE = false>
+template <int D, class F, class Src, bool HIST, bool WIDE = false, bool ODD = false>
 __global__ __launch_bounds__(BLOCK, Src::kInterior ? MinWaves<F>::value : 1) void k_vegas_iter(VegasArgs a, F f, Src src,
                                                                           double* __restrict__ partials) {
   extern __shared__ __align__(16) double lds[];
@@ -220,7 +220,7 @@ __global__ __launch_bounds__(BLOCK, Src::kInterior ? MinWaves<F>::value : 1) voi
     if constexpr (Src::kInterior) {
       uint32_t k[D];
       src.words(base, i, k);
-      const double jac = grid_map_words<D>(k, a.bins, nb, a.nbD, x, idx);
+      const double jac = grid_map_words<D, ODD>(k, a.bins, nb, a.nbD, x, idx);
       w = eval_inside(ff, x) * jac;
     } else {
       double t[D];
@@ -859,7 +859,10 @@ vgx_status launch_iter_f(vgx_vegas* v, int64_t n, const F& f, const Src& src) {
   const size_t lds =
       sizeof(double) * (size_t)lds_table_offset(!Src::kInterior && F::kStage, D, v->nb, HIST, !F::kStage) +
       extra_lds_bytes(v);
-  if (src.seg_len(0, n) == n)  // one segment: the common case
+  if (Src::kInterior && (v->nb & 1))  // an odd bin count's half step in the Philox map
+    hipLaunchKernelGGL((k_vegas_iter<D, F, Src, HIST, true, Src::kInterior>), dim3(grid), dim3(BLOCK), lds, v->stream,
+                       a, f, src, v->partials);
+  else if (src.seg_len(0, n) == n)  // one segment: the common case
     hipLaunchKernelGGL((k_vegas_iter<D, F, Src, HIST, false>), dim3(grid), dim3(BLOCK), lds, v->stream, a, f, src,
                        v->partials);
   else
@@ -1255,7 +1258,7 @@ static hipError_t upload_grid(vgx_vegas* v) {
   for (int j = 0; j < v->dim; ++j)
     for (int k = 0; k < v->nb; ++k) {
       const double* p = e + (size_t)j * (v->nb + 1) + k;
-      b[(size_t)j * v->nb + k] = grid_bin(p[0], p[1], v->nb);
+      b[(size_t)j * v->nb + k] = grid_bin(p[0], p[1]);
     }
   return hipMemcpyAsync(v->edges, e, sizeof(double) * v->grid_doubles(), hipMemcpyHostToDevice, v->stream);
 }

@@ -99,21 +99,20 @@ __device__ __forceinline__ double grid_map_t(const double (&t)[D], const double*
 // The grid map of Philox words k_j, u_j = (k_j + 1/2) 2^-32: one 64-bit
 // multiply-add k_j N + floor(N/2) has the bin in its upper word and the position
 // in it, f_j 2^-32 (for odd N less half a step), in its lower, both exact.
-// The bins' table holds (e_i, w_i 2^-32), for odd N e_i moved by that half step,
-// so that x = e_i + f_j w_i is one FMA and the width needs no subtraction;
-// for even N x is bit for bit that of the map above.  Per dimension
-// two instructions find the bin and the position (the conversion to FP64,
-// scaling, truncation and fraction were four) and one subtraction goes: with
-// the leaner exponential 111 -> 100 VALU instructions per sample for the d = 4
-// Gaussian, 3.35 -> 2.95 ms for 1e9 samples.  The table is read
-// from global memory, one 16-byte load per dimension served by the L1 (a few
-// KB): the LDS's load is the histogram's atomics and the integrand's tables.
-// J = nbDs prod_j w_j 2^-32, nbDs = (N 2^32)^D.
-__host__ __device__ inline double2 grid_bin(double lo, double hi, int nb) {
-  const double w = (hi - lo) * 0x1p-32;
-  return double2{(nb & 1) ? fma(0.5, w, lo) : lo, w};
-}
-template <int D>
+// The bins' table holds (e_i, w_i 2^-32), so that x = e_i + f_j w_i is one FMA
+// and the width needs no subtraction; x is bit for bit that of the map above.
+// Per dimension two instructions find the bin and the position (the
+// conversion to FP64, scaling, truncation and fraction were four) and one
+// subtraction goes: with the leaner exponential 111 -> 100 VALU instructions
+// per sample for the d = 4 Gaussian, 3.35 -> 2.95 ms for 1e9 samples.  ODD adds
+// the half step, one FP64 addition per dimension, in kernels for odd counts (51
+// bins, 2e8 samples: 604 -> 653 us; in the table instead, it rounds every edge
+// once more, and as a branch per sample it cost even counts registers and moves).
+// The table is read from global memory, one 16-byte load per dimension served
+// by the L1 (a few KB): the LDS's load is the histogram's atomics and the
+// integrand's tables.  J = nbDs prod_j w_j 2^-32, nbDs = (N 2^32)^D.
+__host__ __device__ inline double2 grid_bin(double lo, double hi) { return double2{lo, (hi - lo) * 0x1p-32}; }
+template <int D, bool ODD>
 __device__ __forceinline__ double grid_map_words(const uint32_t (&k)[D], const double2* __restrict__ bins, int nb,
                                                  double nbDs, double (&x)[D], int (&idx)[D]) {
   double jw = nbDs;  // first, so that no partial product leaves the FP64 range before J does
@@ -124,7 +123,8 @@ __device__ __forceinline__ double grid_map_words(const uint32_t (&k)[D], const d
     asm("" : "+v"(i));  // keeps the shift below apart from the 64-bit one
     // a 32-bit byte offset from the uniform base (a scalar-base load)
     const double2 e = *(const double2*)((const char*)(bins + j * nb) + (i << 4));
-    x[j] = fma((double)(uint32_t)p, e.y, e.x);
+    const double f = (double)(uint32_t)p;
+    x[j] = fma(ODD ? f + 0.5 : f, e.y, e.x);
     jw *= e.y;
     idx[j] = (int)i;
   }
@@ -341,7 +341,7 @@ __device__ inline void refine_dim(double* __restrict__ ej, double2* __restrict__
   }
   __syncthreads();
   for (int k = lane; k < nb; k += 64)
-    bj[k] = grid_bin(k == 0 ? e[0] : en[k], k == nb - 1 ? e[nb] : en[k + 1], nb);
+    bj[k] = grid_bin(k == 0 ? e[0] : en[k], k == nb - 1 ? e[nb] : en[k + 1]);
 }
 
 // The context's pinned memory; the grid (edges and bins) follows.
