@@ -372,12 +372,100 @@ __device__ __forceinline__ int wave_max_last(int v) {
 }
 
 // Several members of a PDF set at the same points (the thesis's multi-member
-// evaluation for FastKernel-type convolutions): a lane takes one point of
-// members blockIdx.y, blockIdx.y + gridDim.y, ..., so a wave's stores are
-// contiguous and the cells and weights, which do not depend on the member, are
-// found once for all of them; a set of N_rep members at a few thousand points
-// still fills the chip.  The values are the weights and the summation order of
-// k_pdf_interp.
+// evaluation for FastKernel-type convolutions): blockIdx.y is the member, so
+// a wave takes 64 consecutive points of one member and its stores are
+// contiguous; a set of N_rep members at a few thousand points still fills the
+// chip.  One (point, member) per lane, each lane reading its stencil rows as
+// 16-byte loads, in the weights and summation order of k_pdf_interp.  Outside
+// the grid: NaN (counted once per point, by member 0), whatever the context's
+// extrapolation mode.
+template <typename OutT, typename ValT, int NF>
+__global__ __launch_bounds__(256) void k_pdf_members(PdfKernelArgs g, int64_t n, int64_t member_stride,
+                                                     const double* __restrict__ qx, const double* __restrict__ qq2,
+                                                     const double* __restrict__ kx, const double* __restrict__ klx,
+                                                     const double* __restrict__ kq2, const double* __restrict__ klq2,
+                                                     const ValT* __restrict__ vals, OutT* __restrict__ out,
+                                                     unsigned long long* __restrict__ oor) {
+  constexpr int NFM = NF > 0 ? NF : VGX_MAX_FLAV;
+  extern __shared__ double lds[];
+  double* sx = lds;
+  double* slx = sx + g.n_x;
+  const int nqt = g.q_off[g.n_sub];
+  double* sq2 = slx + g.n_x;
+  double* slq2 = sq2 + nqt;
+  for (int k = threadIdx.x; k < g.n_x; k += blockDim.x) { sx[k] = kx[k]; slx[k] = klx[k]; }
+  for (int k = threadIdx.x; k < nqt; k += blockDim.x) { sq2[k] = kq2[k]; slq2[k] = klq2[k]; }
+  __syncthreads();
+  const int nf = NF > 0 ? NF : g.n_flav;
+  const int m = blockIdx.y;
+  const ValT* Vm = vals + (int64_t)m * member_stride;
+  OutT* om = out + (int64_t)m * nf * n;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += stride) {
+    const double x = qx[q];
+    const double q2 = qq2[q];
+    int s = -1;
+    for (int k = 0; k < g.n_sub; ++k) {
+      const bool last = (k == g.n_sub - 1);
+      if (q2 >= g.q2_lo[k] && (q2 < g.q2_hi[k] || (last && q2 <= g.q2_hi[k]))) s = k;
+    }
+    if (s < 0 || !(x >= sx[0] && x <= sx[g.n_x - 1])) {
+      for (int f = 0; f < nf; ++f) om[(int64_t)f * n + q] = (OutT)NAN;
+      if (m == 0) atomicAdd(oor, 1ull);
+      continue;
+    }
+    const int nq = g.nq[s];
+    const double* lq = slq2 + g.q_off[s];
+    const int i = find_cell(sx, g.n_x, x);
+    const int j = find_cell(sq2 + g.q_off[s], nq, q2);
+    const double a = log(x), b = log(q2);
+    const ValT* V = Vm + (int64_t)g.q_off[s] * g.n_x * nf;
+    double acc[NFM];
+#pragma unroll
+    for (int f = 0; f < NFM; ++f) acc[f] = 0.0;
+    if (i >= 1 && i <= g.n_x - 3 && j >= 1 && j <= nq - 3) {
+      const double ha = slx[i + 1] - slx[i];
+      const double hb = lq[j + 1] - lq[j];
+      double cx[4], cq[4];
+      hermite_weights((a - slx[i]) / ha, ha / (slx[i] - slx[i - 1]), ha / (slx[i + 2] - slx[i + 1]), cx);
+      hermite_weights((b - lq[j]) / hb, hb / (lq[j] - lq[j - 1]), hb / (lq[j + 2] - lq[j + 1]), cq);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const ValT* row = V + ((int64_t)(j - 1 + r) * g.n_x + (i - 1)) * nf;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const double w = cq[r] * cx[k];
+          const ValT* node = row + k * nf;
+#pragma unroll
+          for (int f = 0; f < NFM; ++f)
+            if (f < nf) acc[f] = fma(w, (double)node[f], acc[f]);
+        }
+      }
+    } else {
+      const double ta = (a - slx[i]) / (slx[i + 1] - slx[i]);
+      const double tb = (b - lq[j]) / (lq[j + 1] - lq[j]);
+      const double w[4] = {(1.0 - ta) * (1.0 - tb), ta * (1.0 - tb), (1.0 - ta) * tb, ta * tb};
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        const ValT* row = V + ((int64_t)(j + r) * g.n_x + i) * nf;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const ValT* node = row + k * nf;
+#pragma unroll
+          for (int f = 0; f < NFM; ++f)
+            if (f < nf) acc[f] = fma(w[2 * r + k], (double)node[f], acc[f]);
+        }
+      }
+    }
+#pragma unroll
+    for (int f = 0; f < NFM; ++f)
+      if (f < nf) om[(int64_t)f * n + q] = (OutT)acc[f];
+  }
+}
+
+// The same for larger calls: a lane takes one point of members blockIdx.y,
+// blockIdx.y + gridDim.y, ..., so the cells and weights, which do not depend on
+// the member, are found once for all of them.
 //
 // Read from memory, a lane's 16 nodes are 88 (FP64, 11 flavours) 16-byte loads,
 // and the L1 returns 64 bytes per clock whatever the lanes share: 98 loads
@@ -388,8 +476,7 @@ __device__ __forceinline__ int wave_max_last(int v) {
 // bytes, and read back at 128 bytes per clock, lanes of one cell in one
 // access (100 members at 2415 points, FP64: 17.6 -> 12.7 us; 400 at 5000: 99.7
 // -> 45).  Points far apart (a box too large) read memory (400 x 5000 random
-// points: 727 -> 482 us, by the weights found once).  Outside the grid: NaN
-// (counted once per point), whatever the context's extrapolation mode.
+// points: 727 -> 482 us, by the weights found once).
 template <typename ValT, int NF, int W>
 __device__ __forceinline__ void members_sums(double (&acc)[NF > 0 ? NF : VGX_MAX_FLAV], const ValT* V, int64_t row,
                                              int node_stride, int nf, const double (&cx)[4], const double (&cq)[4]) {
@@ -437,14 +524,12 @@ __host__ __device__ constexpr int box_stride(int nf) {
   return (nf + (int)(16 / sizeof(ValT)) - 1) & ~((int)(16 / sizeof(ValT)) - 1);
 }
 
-template <typename OutT, typename ValT, int NF, bool BOX>
-__global__ __launch_bounds__(256, BOX && NF > 0 ? 4 : 1) void k_pdf_members(PdfKernelArgs g, int64_t n, int n_members, int64_t member_stride,
-                                                     int box_bytes,
-                                                     const double* __restrict__ qx, const double* __restrict__ qq2,
-                                                     const double* __restrict__ kx, const double* __restrict__ klx,
-                                                     const double* __restrict__ kq2, const double* __restrict__ klq2,
-                                                     const ValT* __restrict__ vals, OutT* __restrict__ out,
-                                                     unsigned long long* __restrict__ oor) {
+template <typename OutT, typename ValT, int NF>
+__global__ __launch_bounds__(256, NF > 0 ? 4 : 1) void k_pdf_members_box(
+    PdfKernelArgs g, int64_t n, int n_members, int64_t member_stride, int box_bytes, const double* __restrict__ qx,
+    const double* __restrict__ qq2, const double* __restrict__ kx, const double* __restrict__ klx,
+    const double* __restrict__ kq2, const double* __restrict__ klq2, const ValT* __restrict__ vals,
+    OutT* __restrict__ out, unsigned long long* __restrict__ oor) {
   constexpr int NFM = NF > 0 ? NF : VGX_MAX_FLAV;
   extern __shared__ __align__(16) double lds[];
   double* sx = lds;
@@ -501,35 +586,29 @@ __global__ __launch_bounds__(256, BOX && NF > 0 ? 4 : 1) void k_pdf_members(PdfK
         r0 = g.q_off[s] + j - (full ? 1 : 0);
       }
     }
-    bool boxed = false;
-    int xlo = 0, rlo = 0, bx = 0, br = 0;
-    if constexpr (BOX) {
-      const int w1 = full ? 3 : 1, none = -(1 << 30);
-      const int e0 = wave_max_last(in ? -i0 : none), e1 = wave_max_last(in ? i0 + w1 : none);
-      const int e2 = wave_max_last(in ? -r0 : none), e3 = wave_max_last(in ? r0 + w1 : none);
-      __syncthreads();  // ext has been read
-      if ((threadIdx.x & 63) == 63) {
-        const int wv = threadIdx.x >> 6;
-        ext[wv][0] = e0; ext[wv][1] = e1; ext[wv][2] = e2; ext[wv][3] = e3;
-      }
-      __syncthreads();
-      int lim[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) lim[c] = max(max(ext[0][c], ext[1][c]), max(ext[2][c], ext[3][c]));
-      xlo = -lim[0];
-      rlo = -lim[2];
-      bx = lim[1] - xlo + 1;  // negative: no point inside
-      br = lim[3] - rlo + 1;
-      boxed = bx > 0 && (int64_t)bx * br * NS * (int)sizeof(ValT) <= box_bytes;
+    const int w1 = full ? 3 : 1, none = -(1 << 30);
+    const int e0 = wave_max_last(in ? -i0 : none), e1 = wave_max_last(in ? i0 + w1 : none);
+    const int e2 = wave_max_last(in ? -r0 : none), e3 = wave_max_last(in ? r0 + w1 : none);
+    __syncthreads();  // ext has been read
+    if ((threadIdx.x & 63) == 63) {
+      const int wv = threadIdx.x >> 6;
+      ext[wv][0] = e0; ext[wv][1] = e1; ext[wv][2] = e2; ext[wv][3] = e3;
     }
+    __syncthreads();
+    int lim[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) lim[c] = max(max(ext[0][c], ext[1][c]), max(ext[2][c], ext[3][c]));
+    const int xlo = -lim[0], rlo = -lim[2];
+    const int bx = lim[1] - xlo + 1;  // negative: no point inside
+    const int br = lim[3] - rlo + 1;
+    const bool boxed = bx > 0 && (int64_t)bx * br * NS * (int)sizeof(ValT) <= box_bytes;
     const int64_t row = (int64_t)g.n_x * nf;
-    int m = blockIdx.y;
-    do {
+    for (int m = blockIdx.y; m < n_members; m += ms) {
       const ValT* Vm = vals + m * member_stride;
       double acc[NFM];
 #pragma unroll
       for (int f = 0; f < NFM; ++f) acc[f] = 0.0;
-      if (BOX && boxed) {  // uniform per workgroup
+      if (boxed) {  // uniform per workgroup
         __syncthreads();  // the previous box has been read
         const ValT* src = Vm + rlo * row + (int64_t)xlo * nf;
         const int len = bx * nf;
@@ -561,8 +640,7 @@ __global__ __launch_bounds__(256, BOX && NF > 0 ? 4 : 1) void k_pdf_members(PdfK
         for (int f = 0; f < NFM; ++f)
           if (f < nf) om[(int64_t)f * n + q] = (OutT)acc[f];
       }
-      m += ms;
-    } while (BOX && m < n_members);
+    }
   }
 }
 
@@ -940,11 +1018,23 @@ extern "C" vgx_status pdf_interp(const vgx_pdf* p, int64_t n, const double* x_de
   return VGX_OK;
 }
 
-// Values (members x points) from which the LDS box is used.  Below, the box's
-// setup and the fewer workgroups cost as much as the loads: 400 members at 100
-// points 10.5 us from memory, 12.2 with the box; FP32, whose loads are half as
-// many, 100 at 2415 13.2 and 13.8.
-constexpr int64_t kMembersBox64 = 150000, kMembersBox32 = 450000;
+// Where the LDS box is taken: from these many values (members x points) on, for
+// shapes in which it is not slower, points next to each other (a table) or
+// scattered, than a member per lane.  us per call, per lane / box, table and
+// scattered points:
+//   FP64, 11 flavours: 100 members at 1501 points 14.4 / 12.4 and 71 / 61, 100 at
+//   2415 17.5 / 13.1 and 95 / 69, 200 at 5000 52 / 30 and 367 / 256; the setup
+//   for fewer values costs as much as the loads (100 at 1001 11.0 / 11.1, 100
+//   at 400 8.8 / 12.1), and below 700 points a workgroup's last box holds few
+//   lanes for all members (400 at 401 17.6 / 21.6, 3000 at 257 64 / 116).
+//   FP64, other flavour counts: 170 registers, 100 at 1501 22.7 / 30.3, 200 at
+//   5000 97 / 103: never (random points alone gain, 681 / 482).
+//   FP32, whose loads are half as many: 400 at 1501 32 / 23 and 112 / 107, 200 at
+//   5000 39 / 31 and 153 / 139, but 200 at 2415 83 / 84 and 400 at 1001 70 / 82
+//   scattered; with workgroups less than nine tenths full 400 at 1537 33 / 26 and 113 /
+//   117; 1 at 700001 27 / 29 (no weights to share); one flavour 200 at 5000 35 / 37
+//   and 61 / 68, five 56 / 46 and 378 / 330.
+constexpr int64_t kMembersBox64 = 150000, kMembersBox32 = 600000;
 constexpr size_t kMembersBox = 32 * 1024;
 
 extern "C" vgx_status pdf_interp_members(const vgx_pdf* p, int64_t n, const double* x_dev, const double* q2_dev,
@@ -965,44 +1055,42 @@ extern "C" vgx_status pdf_interp_members(const vgx_pdf* p, int64_t n, const doub
   g.q_off[p->n_sub] = p->q_off[p->n_sub];
   const int64_t stride = (int64_t)p->q_off[p->n_sub] * p->n_x * p->n_flav;
   const int block = 256;
-  // Small calls: a member per lane, from memory.  Large ones: the LDS box, two
-  // or more members per lane, at most eight blocks per CU.
-  const bool boxed = (int64_t)p->n_members * n >= (out_dtype == VGX_F64 ? kMembersBox64 : kMembersBox32);
+  const bool f11 = p->n_flav == 11;
+  const int64_t values = (int64_t)p->n_members * n;
   const int64_t want = (n + block - 1) / block;
+  const bool boxed = out_dtype == VGX_F64
+                         ? f11 && n >= 700 && values >= kMembersBox64
+                         : p->n_flav >= 5 && p->n_members >= 4 && n >= 1000 && values >= kMembersBox32 &&
+                               10 * n >= 9 * want * block;
   const int64_t room = (int64_t)device_cus() * 8;
-  int64_t gx, gy = p->n_members;
-  if (boxed) {
-    gx = want < room ? want : room;
-    gy = std::min((gy + 1) / 2, (room + gx - 1) / gx);
+  const size_t knots = sizeof(double) * (2 * (size_t)p->n_x + 2 * (size_t)p->q_off[p->n_sub]);
+  hipStream_t st = (hipStream_t)stream;
+  if (!boxed) {  // a member per lane, the chip filled across members
+    const int64_t cap = std::max<int64_t>(room / p->n_members, 1);
+    const dim3 grid((unsigned)(want < cap ? want : cap), (unsigned)p->n_members);
+    auto launch = [&](auto k, const auto* vals, auto* out) {
+      hipLaunchKernelGGL(k, grid, dim3(block), knots, st, g, n, stride, x_dev, q2_dev, p->x, p->lx, p->q2, p->lq2, vals,
+                         out, p->oor);
+    };
+    if (out_dtype == VGX_F64)
+      launch(f11 ? k_pdf_members<double, double, 11> : k_pdf_members<double, double, 0>, p->v64, (double*)out_dev);
+    else
+      launch(f11 ? k_pdf_members<float, float, 11> : k_pdf_members<float, float, 0>, p->v32, (float*)out_dev);
+  } else {  // two or more members per lane, at most eight blocks per CU
+    const int64_t gx = want < room ? want : room;
+    int64_t gy = std::min<int64_t>((p->n_members + 1) / 2, (room + gx - 1) / gx);
     const int64_t each = (p->n_members + gy - 1) / gy;
     gy = (p->n_members + each - 1) / each;  // even shares
-  } else {
-    const int64_t cap = std::max<int64_t>(room / gy, 1);  // the chip filled across members
-    gx = want < cap ? want : cap;
-  }
-  const dim3 grid((unsigned)gx, (unsigned)gy);
-  const size_t knots = sizeof(double) * (2 * (size_t)p->n_x + 2 * (size_t)p->q_off[p->n_sub]);
-  const size_t box =
-      boxed ? std::min(kMembersBox, (kMaxLds - 1024 - std::min(knots, kMaxLds - 1024)) & ~(size_t)15) : 0;
-  const size_t lds = knots + box;
-  hipStream_t st = (hipStream_t)stream;
-  auto launch = [&](auto k, const auto* vals, auto* out) {
-    hipLaunchKernelGGL(k, grid, dim3(block), lds, st, g, n, p->n_members, stride, (int)box, x_dev, q2_dev, p->x, p->lx,
-                       p->q2, p->lq2, vals, out, p->oor);
-  };
-  const bool f11 = p->n_flav == 11;
-  if (out_dtype == VGX_F64) {
-    double* o = (double*)out_dev;
-    if (boxed) f11 ? launch(k_pdf_members<double, double, 11, true>, p->v64, o)
-                   : launch(k_pdf_members<double, double, 0, true>, p->v64, o);
-    else f11 ? launch(k_pdf_members<double, double, 11, false>, p->v64, o)
-             : launch(k_pdf_members<double, double, 0, false>, p->v64, o);
-  } else {
-    float* o = (float*)out_dev;
-    if (boxed) f11 ? launch(k_pdf_members<float, float, 11, true>, p->v32, o)
-                   : launch(k_pdf_members<float, float, 0, true>, p->v32, o);
-    else f11 ? launch(k_pdf_members<float, float, 11, false>, p->v32, o)
-             : launch(k_pdf_members<float, float, 0, false>, p->v32, o);
+    const dim3 grid((unsigned)gx, (unsigned)gy);
+    const size_t box = std::min(kMembersBox, (kMaxLds - 1024 - std::min(knots, kMaxLds - 1024)) & ~(size_t)15);
+    auto launch = [&](auto k, const auto* vals, auto* out) {
+      hipLaunchKernelGGL(k, grid, dim3(block), knots + box, st, g, n, p->n_members, stride, (int)box, x_dev, q2_dev,
+                         p->x, p->lx, p->q2, p->lq2, vals, out, p->oor);
+    };
+    if (out_dtype == VGX_F64)
+      launch(k_pdf_members_box<double, double, 11>, p->v64, (double*)out_dev);
+    else
+      launch(f11 ? k_pdf_members_box<float, float, 11> : k_pdf_members_box<float, float, 0>, p->v32, (float*)out_dev);
   }
   VGX_HIP(hipGetLastError());
   return VGX_OK;
