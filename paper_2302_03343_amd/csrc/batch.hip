@@ -42,15 +42,22 @@ namespace vgx {
 
 constexpr int BB_MAX = 256;  // launch bound of the persistent kernel
 // A tile's histogram in LDS: [dim nb][columns] doubles, lane l adding into
-// column l mod columns, up to 16 columns per integral, as many as fit in
-// kColsLds (four workgroups per CU).  LDS executes an FP64 atomic 16 lanes at a time,
+// column l mod columns, up to 16 columns per integral, as many as fit in the
+// workgroup's LDS.  LDS executes an FP64 atomic 16 lanes at a time,
 // each group as often as its fullest bank pair has lanes: with random bins
 // 27.6 clocks per wave instruction, with 8 columns 18.0, with 16 10.3.
-constexpr size_t kColsLds = 40 * 1024;
-constexpr int kMaxColsLog2 = 4;
-inline int hist_shift(int dim, int nb) {
+// The registers allow two waves per SIMD, eight per CU, and the columns must
+// not keep workgroups of them away: 160 KB over the workgroups, less the
+// kernel's own LDS, and at most 40 KB.  16 integrals of 10 x 64 bins and 2e6
+// samples: 64 threads (eight workgroups) 620 us with 40 KB, 401 now; 128 (four)
+// 420 and 381; 256 (two) 351, and 362 with a few bytes less than 40 KB, which
+// halves the columns here.
+constexpr size_t kColsLds = 40 * 1024, kOwnLds = 256;
+constexpr int kMaxColsLog2 = 4, kWavesPerCu = 8;
+inline int hist_shift(int dim, int nb, int block) {
+  const size_t fair = (size_t)160 * 1024 / (kWavesPerCu * 64 / block) - kOwnLds, room = fair < kColsLds ? fair : kColsLds;
   int s = 0;
-  while (s < kMaxColsLog2 && (sizeof(double) * dim * nb) << (s + 1) <= kColsLds) ++s;
+  while (s < kMaxColsLog2 && (sizeof(double) * dim * nb) << (s + 1) <= room) ++s;
   return s;
 }
 
@@ -346,10 +353,16 @@ vgx_status enqueue_iteration(vgx_batch* b, hipStream_t st, bool refine) {
   return VGX_OK;
 }
 
-// Block size of the persistent kernel and a grid of as many workgroups as
-// can be resident at once (the kernel's occupancy at that block size): more
-// would only start once the tile queue is empty.
+// Block size of the persistent kernel, the columns of its LDS histograms, and
+// a grid of as many workgroups as can be resident at once (the kernel's
+// occupancy at that block size): more would only start once the tile queue is
+// empty.
 vgx_status set_block(vgx_batch* b, int block) {
+  b->lds = 0;
+  for (BatchItem& it : b->items) {
+    it.shift = hist_shift(it.dim, it.nb, block);
+    b->lds = std::max(b->lds, (sizeof(double) * it.dim * it.nb) << it.shift);
+  }
   int per_cu = 0;
   const void* k = b->odd ? reinterpret_cast<const void*>(&k_batch<true>) : reinterpret_cast<const void*>(&k_batch<false>);
   VGX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, block, b->lds));
@@ -440,7 +453,6 @@ extern "C" vgx_status batch_create(vgx_vegas* const* ctxs, int32_t count, const 
     it.prec = c->prec;
     it.dim = c->dim;
     it.nb = c->nb;
-    it.shift = hist_shift(c->dim, c->nb);
     it.sid = c->stream_id;
     it.k0 = (uint32_t)c->seed;
     it.k1 = (uint32_t)(c->seed >> 32);
@@ -454,7 +466,6 @@ extern "C" vgx_status batch_create(vgx_vegas* const* ctxs, int32_t count, const 
     it.comb = c->comb;
     it.prm = c->prm;
     b->items[k] = it;
-    b->lds = std::max(b->lds, (sizeof(double) * c->dim * c->nb) << it.shift);
     b->odd |= (it.nb & 1) != 0;
     b->max_cols = it.pstride > b->max_cols ? it.pstride : b->max_cols;
   }
