@@ -1438,6 +1438,7 @@ extern "C" vgx_status vegas_sample(vgx_vegas* v, int64_t first, int64_t n, int32
   VGX_CHECK(v, "vegas_sample: null context");
   VGX_CHECK(n >= 0 && first >= 0, "vegas_sample: negative range");
   if (n == 0 || (!u && !g)) return VGX_OK;
+  v->tail = true;  // a batch on another stream must not refine the grid under it
   return launch_sample(v, first, n, iteration, u, g);
 }
 

@@ -42,3 +42,23 @@ def test_batch_follows_the_contexts_stream(vgx, order):
     got1, rec1, res1, grid1 = run(vgx, order, one, one)
     assert got == got1 and rec == rec1 and res == res1
     assert np.array_equal(grid, grid1)
+
+
+def test_batch_refines_after_the_samples_are_drawn(vgx):
+    """vegas_sample reads the grid on the context's stream; a batch refines it on another."""
+    import torch
+    own, batch = torch.cuda.Stream(), torch.cuda.Stream()
+    v = vgx.vegas_create(vgx.GAUSS, DIM, NB, 1.5, 9, 1, vgx.F64, np.array([0.4, 0.5, 0.6, 0.2, 0.1, 0.3]), stream=own)
+    b = vgx.batch_create([v], [N], 1024, 64, stream=batch)
+    try:
+        want, got = (torch.empty(LONG, dtype=torch.float64, device="cuda") for _ in "wg")
+        torch.cuda.synchronize()
+        vgx.vegas_sample(v, 0, LONG, 7, g=want)
+        torch.cuda.synchronize()
+        vgx.vegas_sample(v, 0, LONG, 7, g=got)
+        vgx.batch_iterate(b, 0, 1)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+    finally:
+        vgx.batch_destroy(b)
+        vgx.vegas_destroy(v)
