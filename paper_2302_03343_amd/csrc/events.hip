@@ -19,7 +19,7 @@
 //
 // Both kernels were bound by the FP64 VALU work of the library's log, sincospi,
 // sqrt and divisions (1020 and 1608 instructions per event at n = 4); math64.h
-// has forms for the ranges that occur here (about 800 and 900).  1e7 events
+// has forms for the ranges that occur here (massive 916).  1e7 events
 // of 4: massless 0.34 -> 0.25 ms (5.4 TB/s of the 136 bytes an event that are
 // written: the HBM's rate for 17 streams), massive 0.51 -> 0.34 ms (VALU).
 //

@@ -468,15 +468,14 @@ __global__ __launch_bounds__(256) void k_pdf_members(PdfKernelArgs g, int64_t n,
 // the member, are found once for all of them.
 //
 // Read from memory, a lane's 16 nodes are 88 (FP64, 11 flavours) 16-byte loads,
-// and the L1 returns 64 bytes per clock whatever the lanes share: 98 loads
-// per wave took two thirds of the kernel's time.  The points of a table are
+// and the L1 returns 64 bytes per clock whatever the lanes share.  The points of a table are
 // neighbours, so the workgroup's stencils lie in a box of few nodes: where
 // the box (from the smallest to the largest node index on each axis) fits in
 // box_bytes of LDS, it is copied there, a node padded to a multiple of 16
 // bytes, and read back at 128 bytes per clock, lanes of one cell in one
-// access (100 members at 2415 points, FP64: 17.6 -> 12.7 us; 400 at 5000: 99.7
-// -> 45).  Points far apart (a box too large) read memory (400 x 5000 random
-// points: 727 -> 482 us, by the weights found once).
+// access (100 members at 2415 points, FP64: 17.5 -> 13.1 us; 200 at 5000: 52 ->
+// 30).  Points far apart (a box too large) read memory (200 at 5000 random
+// points: 367 -> 256 us, by the weights found once).
 template <typename ValT, int NF, int W>
 __device__ __forceinline__ void members_sums(double (&acc)[NF > 0 ? NF : VGX_MAX_FLAV], const ValT* V, int64_t row,
                                              int node_stride, int nf, const double (&cx)[4], const double (&cq)[4]) {

@@ -2,28 +2,29 @@
 // fill the chip.
 //
 // Gathering each query's stencil from the L2 is bound by the texture
-// addresser: 16-byte gathers from an L2-resident table take 49 to 120 cycles
-// per wave instruction and CU, depending on the node stride, while random
-// 16-byte reads of LDS take 13.4 (5.2 without bank conflicts; probe at
-// 16 waves per CU).  All flavours of a grid do not fit in a CU's 160 KB, but
+// addresser: 16-byte gathers of one query per lane from an L2-resident table
+// take 49 to 122 clocks per wave instruction and CU, depending on the node
+// stride (26 to 28 where neighbouring lanes share a node, as the gathering
+// kernel arranges, with fewer queries per instruction), while random 16-byte
+// reads of LDS take 13.4 (5.2 without bank conflicts; probe at 16 waves per CU).  All flavours of a grid do not fit in a CU's 160 KB, but
 // 16 bytes of every node do (two FP64 or four FP32 flavours of 196 x 50
 // nodes: 156.8 KB).  So a workgroup stages one group of flavours of the whole
 // grid and evaluates that group for its queries; outputs stay
 // structure-of-arrays and coalesced.  Two ways to cover the groups:
 //   * one group per workgroup, for its lifetime: each group locates the
-//     queries again (about 100 of 190 VALU instructions per query and group
-//     in FP64), nothing is stored in between;
+//     queries again, nothing is stored in between;
 //   * all groups in turn (FP64, whose six groups locate most often): the
 //     workgroup locates a tile of queries once and leaves cells and fractions
 //     (16 bytes a query) where the first group's outputs will go; every
 //     thread writes and reads only its own queries' words, the first group
 //     comes last, and its outputs replace them.
-// 1e8 queries: FP64 8.2 -> 5.5 ms (1.9 TB/s of the 104 bytes a query that
-// have to move), FP32 5.9 -> 3.75 ms.  Both pipes are about three quarters
-// busy (FP64: VALU 0.74 of its issue rate, LDS 0.6 to 0.8 of its cycles);
-// ordering each query's rows so that the lanes of an LDS cycle fall on
-// different banks took the conflicts down by 38 % and the time by less than
-// 1 %, and is not kept.
+// 1e8 queries: FP64 8.2 -> 5.3 ms (2.0 TB/s of the 104 bytes a query that
+// have to move), FP32 5.9 -> 3.75 ms.  Counters of the FP64 kernel at 1e8: LDS
+// busy 0.75 of the cycles (bank conflicts 0.49), VALU issue 0.52, and the
+// records come back from beyond the L2 (21.8 GB read and written past it); of
+// the FP32 kernel at 1e6, copying the nodes in included: LDS 0.49, VALU 0.52.
+// Ordering each query's rows so that the lanes of an LDS cycle fall on
+// different banks lowered the conflicts, not the time (1 %), and is not kept.
 //
 // Locating a query in one axis:
 //   * cell: the top word of the FP64 value is a piecewise-linear logarithm;

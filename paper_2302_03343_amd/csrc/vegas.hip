@@ -15,12 +15,15 @@
 //   * one fused kernel per iteration, grid-stride over the sample indices
 //     (32-bit within segments whose counters do not carry), no per-sample
 //     buffers: uniforms are regenerated from the counter;
-//   * the grid edges (d x (N+1) FP64) and the per-workgroup histogram
-//     (d x N FP64, LDS atomics) live in LDS; integrand tables (the PDF rows
-//     of the hadronic integrands) too, staged once per context and copied
-//     by every workgroup;
-//   * S1, S2 are FP64 sums compensated per 16-sample chunk (Neumaier), wave
-//     reduced with cross-lane shuffles and written as per-workgroup partials;
+//   * the workgroup's histogram (d x N FP64 per copy, LDS atomics) and the
+//     integrand tables (the PDF rows of the hadronic integrands, staged once
+//     per context and copied by every workgroup) live in LDS; the kernels that
+//     draw Philox words read the grid as the bins' table (d x N pairs of an edge
+//     and a width) from global memory, served by the L1; caller points of
+//     integrands with tables, the flow's points with them, and vegas_sample
+//     stage the edges (d x (N+1) FP64) in LDS too;
+//   * S1, S2 are FP64 sums compensated per 16-sample chunk (Neumaier), added up
+//     over a wave by DPP and written as per-workgroup partials;
 //     a second kernel reduces the partials in a fixed order (no float
 //     atomics across workgroups), computes E and var(E), and updates the
 //     inverse-variance combination, all on the device;
