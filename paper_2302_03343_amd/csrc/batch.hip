@@ -45,7 +45,7 @@ constexpr int BB_MAX = 256;  // launch bound of the persistent kernel
 // column l mod columns, up to 16 columns per integral, as many as fit in the
 // workgroup's LDS.  LDS executes an FP64 atomic 16 lanes at a time,
 // each group as often as its fullest bank pair has lanes: with random bins
-// 27.5 clocks per wave instruction, with 8 columns 17.9, with 16 10.2 (probe).
+// 27.5 clocks per wave instruction, with 8 columns 17.9, with 16 10.2.
 // The registers allow two waves per SIMD, eight per CU, and the columns must
 // not keep workgroups of them away: 160 KB over the workgroups, less the
 // kernel's own LDS, and at most 40 KB.  16 integrals of 10 x 64 bins and 2e6

@@ -22,7 +22,8 @@
 // have to move), FP32 5.9 -> 3.75 ms.  Counters of the FP64 kernel at 1e8: LDS
 // busy 0.75 of the cycles (bank conflicts 0.49), VALU issue 0.52, and the
 // records come back from beyond the L2 (21.8 GB read and written past it); of
-// the FP32 kernel at 1e6, copying the nodes in included: LDS 0.49, VALU 0.52.
+// the FP32 kernel at 1e8: LDS 0.69 (0.45), VALU 0.74, at 1e6, copying the nodes
+// in included, 0.49 and 0.52.
 // Ordering each query's rows so that the lanes of an LDS cycle fall on
 // different banks lowered the conflicts, not the time (1 %), and is not kept.
 //

@@ -103,7 +103,7 @@ __device__ __forceinline__ double grid_map_t(const double (&t)[D], const double*
 // and the width needs no subtraction; x is bit for bit that of the map above.
 // Per dimension two instructions find the bin and the position (the
 // conversion to FP64, scaling, truncation and fraction were four) and one
-// subtraction goes: with the leaner exponential 111 -> 100 VALU instructions
+// subtraction goes: with the leaner exponential 111 -> 97 VALU instructions
 // per sample for the d = 4 Gaussian; 1e9 samples, 20 launches of each on one
 // GPU: 3.45 -> 3.14 ms on average, 3.28 -> 2.96 the fastest.  ODD adds
 // the half step, one FP64 addition per dimension, in kernels for odd counts (51
