@@ -846,8 +846,9 @@ double pow_int(double b, int e) {
   return r;
 }
 
-// Samples per thread up to which one histogram copy per wave is kept.
-constexpr int kFewSamples = 4;
+// Samples per thread up to which one histogram copy per wave is kept, and the
+// bins it takes: with fewer the lanes of an atomic meet in them.
+constexpr int kFewSamples = 4, kFewBins = 16;
 
 // Launch helpers dispatching on (kind, prec, D).
 template <int D, class F, class Src, bool HIST>
@@ -856,9 +857,12 @@ vgx_status launch_iter_f(vgx_vegas* v, int64_t n, const F& f, const Src& src) {
               pow_int(v->nb * (Src::kInterior ? 0x1p32 : 1.0), D), v->tables, v->table_bytes};
   const int grid = grid_for(v, n);
   // a few samples per thread: clearing and summing sixteen copies costs more
-  // than their atomics' conflicts (d = 4, 50 bins: 13.2 -> 12.1 us at 1e6 samples, 8.4 -> 7.5 at 3e5; equal
-  // from 2e6 on)
-  if (a.hcopies > BLOCK / 64 && n <= (int64_t)grid * BLOCK * kFewSamples) a.hcopies = BLOCK / 64;
+  // than their atomics' conflicts (d = 4, 50 bins: 13.2 -> 12.1 us at 1e6
+  // samples, 8.4 -> 7.5 at 3e5; equal from 2e6 on), but not with few bins (two, d
+  // = 10, 1e6 samples: 30 us with sixteen copies, 45 with four; twelve bins, 1.8e6
+  // 37.3 and 38.6; none slower from 16 bins on)
+  if (a.hcopies > BLOCK / 64 && v->nb >= kFewBins && n <= (int64_t)grid * BLOCK * kFewSamples)
+    a.hcopies = BLOCK / 64;
   const size_t lds =
       sizeof(double) * (size_t)lds_table_offset(!Src::kInterior && F::kStage, D, v->nb, HIST, !F::kStage) +
       extra_lds_bytes(v);
