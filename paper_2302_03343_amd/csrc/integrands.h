@@ -50,6 +50,7 @@ __device__ __forceinline__ double exp_neg(double e) {
 // the host into p[2D] so that the device does only the data-dependent part.
 template <int D, typename R>
 struct Gauss : NoStage {
+  using Real = R;
   IntegrandParams prm;  // [c_0..c_{D-1}, 1/(s_j sqrt 2) .., norm]
   __device__ __forceinline__ R exponent(const double (&x)[D]) const {
     R e = 0;
@@ -76,6 +77,7 @@ struct Gauss : NoStage {
 // Genz oscillatory: cos(2 pi w_1 + sum_j c_j x_j).  p = [2 pi w_1, c_0 ..].
 template <int D, typename R>
 struct GenzOsc : NoStage {
+  using Real = R;
   IntegrandParams prm;
   __device__ __forceinline__ double eval(const double (&x)[D]) const {
     R a = (R)prm.p[0];
@@ -89,6 +91,7 @@ struct GenzOsc : NoStage {
 // p = [w_0..w_{D-1}, c_0^-2 .. c_{D-1}^-2].
 template <int D, typename R>
 struct GenzPeak : NoStage {
+  using Real = R;
   IntegrandParams prm;
   __device__ __forceinline__ double eval(const double (&x)[D]) const {
     R den = 1;

@@ -174,17 +174,25 @@ __device__ __forceinline__ void stage_tables(F& ff, float* extra, const VegasArg
 // Partial row per workgroup: [S1.s, S1.c, S2.s, S2.c, hist[D][nb]].
 // ---------------------------------------------------------------------------
 // Minimum waves per SIMD an integrand asks of the iteration kernel (its
-// register budget): F::kMinWaves when declared, else 1 (no constraint).
+// register budget): F::kMinWaves when declared, else 1 (no constraint).  The
+// FP64 oscillatory kernel of 12 dimensions takes 131 registers and is held to
+// 128, four waves, without spills (3e7 samples, 64 bins: 350 -> 335 us).
 template <class F, class = void>
 struct MinWaves { static constexpr int value = 1; };
 template <class F>
 struct MinWaves<F, std::void_t<decltype(F::kMinWaves)>> { static constexpr int value = F::kMinWaves; };
+template <>
+struct MinWaves<GenzOsc<12, double>> { static constexpr int value = 4; };
+
+// The grid map of the Philox kernels: the bins' table for even or odd bin
+// counts, or the edges (vegas_internal.h).
+enum GridMap { MAP_BINS = 0, MAP_ODD = 1, MAP_EDGES = 2 };
 
 // Caller points (flow samples) carry a density and an index into memory:
 // the integrand's occupancy bound would make those kernels spill, so they
 // take none.
-template <int D, class F, class Src, bool HIST, bool WIDE = false, bool ODD = false>
-__global__ __launch_bounds__(BLOCK, Src::kInterior ? MinWaves<F>::value : 1) void k_vegas_iter(VegasArgs a, F f, Src src,
+template <int D, class F, class Src, bool HIST, bool WIDE = false, GridMap MAP = MAP_BINS>
+__global__ __launch_bounds__(BLOCK, Src::kInterior && (F::kStage || MAP == MAP_BINS) ? MinWaves<F>::value : 1) void k_vegas_iter(VegasArgs a, F f, Src src,
                                                                           double* __restrict__ partials) {
   extern __shared__ __align__(16) double lds[];
   constexpr bool EDGES = !Src::kInterior && F::kStage;
@@ -223,7 +231,8 @@ __global__ __launch_bounds__(BLOCK, Src::kInterior ? MinWaves<F>::value : 1) voi
     if constexpr (Src::kInterior) {
       uint32_t k[D];
       src.words(base, i, k);
-      const double jac = grid_map_words<D, ODD>(k, a.bins, nb, a.nbD, x, idx);
+      const double jac = MAP == MAP_EDGES ? grid_map_edges<D>(k, a.edges, nb, (nb & 1) ? 0x1p-33 : 0.0, a.nbD, x, idx)
+                                          : grid_map_words<D, MAP == MAP_ODD>(k, a.bins, nb, a.nbD, x, idx);
       w = eval_inside(ff, x) * jac;
     } else {
       double t[D];
@@ -850,11 +859,32 @@ double pow_int(double b, int e) {
 // bins it takes: with fewer the lanes of an atomic meet in them.
 constexpr int kFewSamples = 4, kFewBins = 16;
 
+// Bins over all dimensions from which the Philox map reads the edges instead
+// of the bins' table (0: never).  FP32 kernels have fewer instructions beside
+// the map, so the loads bind earlier; below 8 (10) dimensions the table is never
+// slower.  3e7 samples, us, table / edges: FP32 d = 12 with 64 bins 312 / 300,
+// with 128 322 / 295, d = 8 with 96 207 / 204, with 128 216 / 204; FP64 product
+// peak d = 10 with 128 265 / 258, but d = 9 with 128 238 / 245.  The FP64
+// Gaussian from ten dimensions on reads the edges at any size: with the table it
+// takes 130 registers and more, three waves per SIMD (d = 10 with 16 bins 260 /
+// 248, with 50 277 / 263, d = 11 with 50 304 / 296, d = 12 with 50 325 / 326).
+template <int D, class F, class Src>
+struct LongRows {
+  static constexpr int limit() {
+    if constexpr (!Src::kInterior || F::kStage) return 0;
+    else if constexpr (sizeof(typename F::Real) == 4) return D >= 8 ? 768 : 0;
+    else return D < 10 ? 0 : std::is_same<F, Gauss<D, double>>::value ? 1 : 832;
+  }
+  static constexpr int value = limit();
+};
+
 // Launch helpers dispatching on (kind, prec, D).
 template <int D, class F, class Src, bool HIST>
 vgx_status launch_iter_f(vgx_vegas* v, int64_t n, const F& f, const Src& src) {
+  constexpr int kLong = LongRows<D, F, Src>::value;
+  const bool by_edges = kLong && D * v->nb >= kLong;
   VegasArgs a{n, v->edges, v->bins, v->nb, v->pstride, hist_copies(D, v->nb, !F::kStage),
-              pow_int(v->nb * (Src::kInterior ? 0x1p32 : 1.0), D), v->tables, v->table_bytes};
+              pow_int(v->nb * (Src::kInterior && !by_edges ? 0x1p32 : 1.0), D), v->tables, v->table_bytes};
   const int grid = grid_for(v, n);
   // a few samples per thread: clearing and summing sixteen copies costs more
   // than their atomics' conflicts (d = 4, 50 bins: 13.2 -> 12.1 us at 1e6
@@ -866,15 +896,18 @@ vgx_status launch_iter_f(vgx_vegas* v, int64_t n, const F& f, const Src& src) {
   const size_t lds =
       sizeof(double) * (size_t)lds_table_offset(!Src::kInterior && F::kStage, D, v->nb, HIST, !F::kStage) +
       extra_lds_bytes(v);
-  if (Src::kInterior && (v->nb & 1))  // an odd bin count's half step in the Philox map
-    hipLaunchKernelGGL((k_vegas_iter<D, F, Src, HIST, true, Src::kInterior>), dim3(grid), dim3(BLOCK), lds, v->stream,
-                       a, f, src, v->partials);
-  else if (src.seg_len(0, n) == n)  // one segment: the common case
-    hipLaunchKernelGGL((k_vegas_iter<D, F, Src, HIST, false>), dim3(grid), dim3(BLOCK), lds, v->stream, a, f, src,
-                       v->partials);
-  else
-    hipLaunchKernelGGL((k_vegas_iter<D, F, Src, HIST, true>), dim3(grid), dim3(BLOCK), lds, v->stream, a, f, src,
-                       v->partials);
+  auto launch = [&](auto k) {
+    hipLaunchKernelGGL(k, dim3(grid), dim3(BLOCK), lds, v->stream, a, f, src, v->partials);
+  };
+  if constexpr (kLong == 1) {
+    launch(k_vegas_iter<D, F, Src, HIST, true, MAP_EDGES>);
+  } else {
+    constexpr GridMap kOdd = Src::kInterior ? MAP_ODD : MAP_BINS, kEdges = kLong ? MAP_EDGES : MAP_BINS;
+    if (by_edges) launch(k_vegas_iter<D, F, Src, HIST, true, kEdges>);
+    else if (Src::kInterior && (v->nb & 1)) launch(k_vegas_iter<D, F, Src, HIST, true, kOdd>);
+    else if (src.seg_len(0, n) == n) launch(k_vegas_iter<D, F, Src, HIST, false>);  // one segment: the common case
+    else launch(k_vegas_iter<D, F, Src, HIST, true>);
+  }
   VGX_HIP(hipGetLastError());
   return VGX_OK;
 }

@@ -112,6 +112,11 @@ __device__ __forceinline__ double grid_map_t(const double (&t)[D], const double*
 // The table is read from global memory, one 16-byte load per dimension served
 // by the L1 (a few KB): the LDS's load is the histogram's atomics and the
 // integrand's tables.  J = nbDs prod_j w_j 2^-32, nbDs = (N 2^32)^D.
+//
+// A wave's load touches as many cache lines as the dimension's row has, 16
+// bytes a bin: with many dimensions and bins that binds, and grid_map_edges
+// reads the edges (8 bytes a bin) and takes two more instructions per dimension.
+// Its x and J are the same bit for bit, for both parities.
 __host__ __device__ inline double2 grid_bin(double lo, double hi) { return double2{lo, (hi - lo) * 0x1p-32}; }
 template <int D, bool ODD>
 __device__ __forceinline__ double grid_map_words(const uint32_t (&k)[D], const double2* __restrict__ bins, int nb,
@@ -127,6 +132,25 @@ __device__ __forceinline__ double grid_map_words(const uint32_t (&k)[D], const d
     const double f = (double)(uint32_t)p;
     x[j] = fma(ODD ? f + 0.5 : f, e.y, e.x);
     jw *= e.y;
+    idx[j] = (int)i;
+  }
+  return jw;
+}
+
+// hf: 2^-33 for odd N, else 0; nbD = N^D.
+template <int D>
+__device__ __forceinline__ double grid_map_edges(const uint32_t (&k)[D], const double* __restrict__ edges, int nb,
+                                                 double hf, double nbD, double (&x)[D], int (&idx)[D]) {
+  double jw = nbD;
+#pragma unroll
+  for (int j = 0; j < D; ++j) {
+    const uint64_t p = (uint64_t)k[j] * (uint32_t)nb + (uint32_t)(nb >> 1);
+    uint32_t i = (uint32_t)(p >> 32);
+    asm("" : "+v"(i));
+    const double2_a8 e = *(const double2_a8*)((const char*)(edges + j * (nb + 1)) + (i << 3));
+    const double w = e.y - e.x;
+    x[j] = fma(fma((double)(uint32_t)p, 0x1p-32, hf), w, e.x);
+    jw *= w;
     idx[j] = (int)i;
   }
   return jw;
