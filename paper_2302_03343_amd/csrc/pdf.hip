@@ -888,7 +888,7 @@ extern "C" vgx_status pdf_create_set(const vgx_pdf_desc* d, int32_t n_members, v
     // 16 bytes at a time, up to 12 bytes beyond the last node
     if ((st_ = dev_alloc((void**)&p->v64, sizeof(double) * (nvals + 2))) != VGX_OK) break;
     if ((st_ = dev_alloc((void**)&p->v32, sizeof(float) * (nvals + 4))) != VGX_OK) break;
-    if ((st_ = dev_alloc((void**)&p->oor, sizeof(unsigned long long))) != VGX_OK) break;
+    if ((st_ = dev_alloc((void**)&p->oor, sizeof(unsigned long long) * kOorSlots * kOorStride)) != VGX_OK) break;
     hipError_t e = hipSuccess;
     if (e == hipSuccess) e = hipMemcpyAsync(p->x, p->h_x, sizeof(double) * p->n_x, hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipMemcpyAsync(p->lx, lx, sizeof(double) * p->n_x, hipMemcpyHostToDevice, st);
@@ -898,7 +898,7 @@ extern "C" vgx_status pdf_create_set(const vgx_pdf_desc* d, int32_t n_members, v
     if (e == hipSuccess) e = hipMemsetAsync(p->v64 + nvals, 0, 2 * sizeof(double), st);
     if (e == hipSuccess) e = hipMemcpyAsync(p->v32, v32, sizeof(float) * nvals, hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipMemsetAsync(p->v32 + nvals, 0, 4 * sizeof(float), st);
-    if (e == hipSuccess) e = hipMemsetAsync(p->oor, 0, sizeof(unsigned long long), st);
+    if (e == hipSuccess) e = hipMemsetAsync(p->oor, 0, sizeof(unsigned long long) * kOorSlots * kOorStride, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) st_ = hip_fail(e, "pdf_create copies", __FILE__, __LINE__);
     if (st_ == VGX_OK) st_ = setup_lds(p, st);
@@ -1104,12 +1104,13 @@ extern "C" vgx_status pdf_shape(const vgx_pdf* p, int32_t* n_flav, int32_t* n_me
 
 extern "C" vgx_status pdf_out_of_range(vgx_pdf* p, void* stream, int64_t* count) {
   VGX_CHECK(p && count, "pdf_out_of_range: null argument");
-  unsigned long long c = 0;
+  unsigned long long c = 0, slot[kOorSlots * kOorStride];
   hipStream_t st = (hipStream_t)stream;
-  VGX_HIP(hipMemcpyAsync(&c, p->oor, sizeof(c), hipMemcpyDeviceToHost, st));
+  VGX_HIP(hipMemcpyAsync(slot, p->oor, sizeof(slot), hipMemcpyDeviceToHost, st));
   VGX_HIP(hipStreamSynchronize(st));
-  VGX_HIP(hipMemsetAsync(p->oor, 0, sizeof(c), st));
+  VGX_HIP(hipMemsetAsync(p->oor, 0, sizeof(slot), st));
   VGX_HIP(hipStreamSynchronize(st));
+  for (int k = 0; k < kOorSlots; ++k) c += slot[k * kOorStride];
   *count = (int64_t)c;
   return c ? VGX_ERANGE : VGX_OK;
 }

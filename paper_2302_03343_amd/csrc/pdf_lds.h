@@ -249,7 +249,8 @@ __global__ __launch_bounds__(kLdsBlock) void k_pdf_interp_lds(PdfLdsArgs a, int6
   const int first_wg = g0 * a.wg_full;
   const int wgs = g0 < last ? a.wg_full : (int)gridDim.x - first_wg;
   const int wg = blockIdx.x - first_wg;
-  P p{a, lds_raw, lds_raw + a.node_bytes, ALL ? (const double2*)(lds_raw + a.node_bytes) : ratios, oor, g0 == 0};
+  P p{a, lds_raw, lds_raw + a.node_bytes, ALL ? (const double2*)(lds_raw + a.node_bytes) : ratios,
+      oor + blockIdx.x % kOorSlots * kOorStride, g0 == 0};
   if constexpr (!ALL) {
     copy16(lds_raw + a.node_bytes, tables, a.tab_bytes);
     copy16(lds_raw, nodes + (size_t)g0 * a.node_bytes, a.node_bytes);
