@@ -756,9 +756,10 @@ hipError_t allow_lds() {
   return hipSuccess;
 }
 
-// The tables of the interpolation with the grid in LDS (sync): uploaded, and
-// member 0's nodes regrouped on the device.
-vgx_status setup_lds(vgx_pdf* p, hipStream_t st) {
+// The tables of the interpolation with the grid in LDS (async): uploaded, and
+// member 0's nodes regrouped on the device.  *host is what the upload reads, to
+// be freed after it (null: none).
+vgx_status setup_lds(vgx_pdf* p, hipStream_t st, unsigned char** host) {
   PdfLdsArgs a{};
   if (!pdf_lds_plan(p, a)) return VGX_OK;
   const int n_nodes = p->n_x * p->q_off[p->n_sub];
@@ -769,6 +770,7 @@ vgx_status setup_lds(vgx_pdf* p, hipStream_t st) {
   p->lds_o_n32 = p->lds_o_n64 + (size_t)g64 * a.node_bytes;
   unsigned char* h = (unsigned char*)malloc(p->lds_o_n64);
   if (!h) { set_error("pdf_create: host allocation failed"); return VGX_ENOMEM; }
+  *host = h;
   pdf_lds_fill(p, a, h, (double*)(h + p->lds_o_ratios));
   vgx_status s = dev_alloc((void**)&p->lds_block, p->lds_o_n32 + (size_t)g32 * a.node_bytes);
   if (s == VGX_OK) {
@@ -783,10 +785,8 @@ vgx_status setup_lds(vgx_pdf* p, hipStream_t st) {
     if (e == hipSuccess) e = allow_lds<VGX_EXTRAP_ERROR>();
     if (e == hipSuccess) e = allow_lds<VGX_EXTRAP_FREEZE>();
     if (e == hipSuccess) e = allow_lds<VGX_EXTRAP_CONTINUE>();
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) s = hip_fail(e, "pdf_create tables", __FILE__, __LINE__);
   }
-  free(h);
   p->lds_args = a;
   return s;
 }
@@ -878,6 +878,7 @@ extern "C" vgx_status pdf_create_set(const vgx_pdf_desc* d, int32_t n_members, v
       return VGX_EINVAL;
     }
   }
+  unsigned char* host = nullptr;
   vgx_status st_ = VGX_OK;
   do {
     if ((st_ = dev_alloc((void**)&p->x, sizeof(double) * p->n_x)) != VGX_OK) break;
@@ -899,10 +900,11 @@ extern "C" vgx_status pdf_create_set(const vgx_pdf_desc* d, int32_t n_members, v
     if (e == hipSuccess) e = hipMemcpyAsync(p->v32, v32, sizeof(float) * nvals, hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipMemsetAsync(p->v32 + nvals, 0, 4 * sizeof(float), st);
     if (e == hipSuccess) e = hipMemsetAsync(p->oor, 0, sizeof(unsigned long long) * kOorSlots * kOorStride, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e == hipSuccess) st_ = setup_lds(p, st, &host);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);  // also after an error of the tables: their upload reads host
     if (e != hipSuccess) st_ = hip_fail(e, "pdf_create copies", __FILE__, __LINE__);
-    if (st_ == VGX_OK) st_ = setup_lds(p, st);
   } while (0);
+  free(host);
   free(lx); free(lq); free(v); free(v32);
   if (st_ != VGX_OK) { pdf_destroy(p); return st_; }
   *out = p;

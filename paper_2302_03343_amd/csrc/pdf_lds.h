@@ -361,22 +361,25 @@ inline bool pdf_lds_plan(const vgx_pdf* p, PdfLdsArgs& a) {
   return true;
 }
 
-// Spacing of two knots in the logarithm; zero for a threshold's two.
-inline long double pdf_spacing(const double* knot, int k) {
-  return log1pl(((long double)knot[k + 1] - knot[k]) / knot[k]);
-}
-
 // The tables (tab_bytes) and the stencil ratios (16 bytes per cell, x then
 // Q^2) of a planned grid, from its knots.
 inline void pdf_lds_fill(const vgx_pdf* p, const PdfLdsArgs& a, unsigned char* tab, double* ratios) {
   memset(tab, 0, (size_t)a.tab_bytes);
-  auto axis = [&](const PdfLdsAxis& ax, const double* knot, int o_knot, int o_h, int o_start, int o_end) {
+  // spacings in the logarithm; zero for a threshold's two knots
+  long double hx[kMaxLdsKnots], hq[kMaxLdsKnots];
+  auto spacings = [](const double* knot, int n, long double* h) {
+    for (int k = 0; k + 1 < n; ++k) h[k] = log1pl(((long double)knot[k + 1] - knot[k]) / knot[k]);
+  };
+  spacings(p->h_x, p->n_x, hx);
+  spacings(p->h_q2, p->q_off[p->n_sub], hq);
+  auto axis = [&](const PdfLdsAxis& ax, const double* knot, const long double* hl, int o_knot, int o_h, int o_start,
+                  int o_end) {
     double* k2 = (double*)(tab + o_knot);
     double* h = (double*)(tab + o_h);
     for (int k = 0; k <= ax.n; ++k) {
       k2[2 * k] = k + 1 < ax.n ? knot[k] : INFINITY;
       k2[2 * k + 1] = k + 1 < ax.n ? 1.0 / knot[k] : 0.0;
-      if (k < ax.n) h[k] = k + 1 < ax.n && knot[k + 1] > knot[k] ? (double)(1.0L / pdf_spacing(knot, k)) : 0.0;
+      if (k < ax.n) h[k] = k + 1 < ax.n && hl[k] > 0.0L ? (double)(1.0L / hl[k]) : 0.0;
     }
     for (int b = 0; b < o_end - o_start; ++b) {
       // a bucket past the top word's range is never looked up
@@ -387,24 +390,23 @@ inline void pdf_lds_fill(const vgx_pdf* p, const PdfLdsArgs& a, unsigned char* t
       tab[o_start + b] = b == 0 ? 0 : (unsigned char)pdf_host_cell(knot, ax.n, v);
     }
   };
-  axis(a.x, p->h_x, a.o_kx, a.o_hx, a.o_bx, a.o_bq);
-  axis(a.q, p->h_q2, a.o_kq, a.o_hq, a.o_bq, a.tab_bytes);
+  axis(a.x, p->h_x, hx, a.o_kx, a.o_hx, a.o_bx, a.o_bq);
+  axis(a.q, p->h_q2, hq, a.o_kq, a.o_hq, a.o_bq, a.tab_bytes);
   double* lt = (double*)(tab + a.o_log);
   for (int k = 0; k <= kLogTab; ++k) {  // exact at both ends: c = 1, and c = 1/2 with ln 2 as in lds_log1p
     const double c = 1.0 / (1.0 + (double)k / kLogTab);
     lt[2 * k] = c;
     lt[2 * k + 1] = k == 0 ? 0.0 : k == kLogTab ? kLn2 : (double)-logl((long double)c);
   }
-  auto stencil = [&](double* r, const double* knot, int n) {
+  auto stencil = [](double* r, const long double* h, int n) {
     for (int k = 0; k < n; ++k) {
       const bool full = k >= 1 && k <= n - 3;
-      const long double h = full ? pdf_spacing(knot, k) : 0.0L;
-      r[2 * k] = full ? (double)(h / pdf_spacing(knot, k - 1)) : -1.0;
-      r[2 * k + 1] = full ? (double)(h / pdf_spacing(knot, k + 1)) : 0.0;
+      r[2 * k] = full ? (double)(h[k] / h[k - 1]) : -1.0;
+      r[2 * k + 1] = full ? (double)(h[k] / h[k + 1]) : 0.0;
     }
   };
-  stencil(ratios, p->h_x, p->n_x);
-  for (int s = 0; s < p->n_sub; ++s) stencil(ratios + 2 * (p->n_x + p->q_off[s]), p->h_q2 + p->q_off[s], p->nq[s]);
+  stencil(ratios, hx, p->n_x);
+  for (int s = 0; s < p->n_sub; ++s) stencil(ratios + 2 * (p->n_x + p->q_off[s]), hq + p->q_off[s], p->nq[s]);
 }
 
 }  // namespace vgx
