@@ -19,7 +19,8 @@
 //     integrand tables (the PDF rows of the hadronic integrands, staged once
 //     per context and copied by every workgroup) live in LDS; the kernels that
 //     draw Philox words read the grid as the bins' table (d x N pairs of an edge
-//     and a width) from global memory, served by the L1; caller points of
+//     and a width), or with many dimensions and bins as pairs of edges, from
+//     global memory, served by the L1; caller points of
 //     integrands with tables, the flow's points with them, and vegas_sample
 //     stage the edges (d x (N+1) FP64) in LDS too;
 //   * S1, S2 are FP64 sums compensated per 16-sample chunk (Neumaier), added up

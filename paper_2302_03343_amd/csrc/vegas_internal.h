@@ -105,7 +105,7 @@ __device__ __forceinline__ double grid_map_t(const double (&t)[D], const double*
 // conversion to FP64, scaling, truncation and fraction were four) and one
 // subtraction goes: with the leaner exponential 111 -> 97 VALU instructions
 // per sample for the d = 4 Gaussian; 1e9 samples, 20 launches of each on one
-// GPU: 3.45 -> 3.14 ms on average, 3.28 -> 2.96 the fastest.  ODD adds
+// GPU: 3.45 -> 3.17 ms on average, 3.28 -> 2.95 the fastest.  ODD adds
 // the half step, one FP64 addition per dimension, in kernels for odd counts (51
 // bins, 2e8 samples: 604 -> 653 us; in the table instead, it rounds every edge
 // once more, and as a branch per sample it cost even counts registers and moves).
